@@ -317,13 +317,13 @@ int32_t run_layered(chem_dnn *h, int64_t n, int64_t ld, const double *T, const d
   hipError_t e = hipSuccess;
   for (int64_t n0 = 0; n0 < n && e == hipSuccess; n0 += kChunk) {
     const int nc = (int)(n - n0 < kChunk ? n - n0 : kChunk);
-    const int ncb = (nc + 255) / 256 * 16;     // whole 256-cell tiles
+    const int ncb = (nc + 15) / 16;
     PrepArgs pa{T, P, Y, ld, n0, nc, ncb, h->act[0], h->fc, h->dc, h->S};
     e = launch_prep(fmt, pa, s);
     int cur = 0;
     for (int l = 0; l < h->L && e == hipSuccess; ++l) {
       LayerArgs la{h->wpack[l] ? (const uint8_t *)h->wpack[l] : nullptr, h->bias[l], h->act[cur],
-                   h->act[cur ^ 1], h->obuf, h->lR[l], h->lNQ[l], ncb, 16 * ncb, nullptr, 0, 0};
+                   h->act[cur ^ 1], h->obuf, h->lR[l], h->lNQ[l], ncb, 16 * ncb, h->lR[l], h->n_cu, nullptr, 0, 0};
       e = launch_layer(fmt, la, l < h->L - 1, s);
       cur ^= 1;
     }
@@ -775,7 +775,7 @@ int32_t chem_dnn_debug_layers(chem_dnn *h, int64_t n, int64_t ld, const double *
   }
   // layer by layer: one chunk (n <= CHEM_DNN_DEBUG_MAX_CELLS < kChunk)
   const int fmt = h->prec;
-  const int nc = (int)n, ncb = (nc + 255) / 256 * 16;
+  const int nc = (int)n, ncb = (nc + 15) / 16;
   PrepArgs pa{T, P, Y, ld, 0, nc, ncb, h->act[0], h->fc, h->dc, h->S};
   hipError_t e = launch_prep(fmt, pa, s);
   if (e == hipSuccess) e = launch_frag_decode(fmt, h->act[0], ncb, h->widths[0], nc, qin, s);
@@ -783,7 +783,7 @@ int32_t chem_dnn_debug_layers(chem_dnn *h, int64_t n, int64_t ld, const double *
   for (int l = 0; l < h->L && e == hipSuccess; ++l) {
     const bool hidden = l < h->L - 1;
     LayerArgs la{(const uint8_t *)h->wpack[l], h->bias[l], h->act[cur], h->act[cur ^ 1], h->obuf,
-                 h->lR[l], h->lNQ[l], ncb, 16 * ncb, nullptr, 0, 0};
+                 h->lR[l], h->lNQ[l], ncb, 16 * ncb, h->lR[l], h->n_cu, nullptr, 0, 0};
     if (hidden) {
       la.dbg_acc = acc + (size_t)acc_row[l] * nc;
       la.dbg_rows = h->widths[l + 1];
@@ -918,13 +918,13 @@ int32_t chem_prop_eval(chem_prop *h, int64_t n, int64_t ld, const double *x, dou
   hipError_t e = hipSuccess;
   for (int64_t n0 = 0; n0 < n && e == hipSuccess; n0 += h->chunk) {
     const int nc = (int)(n - n0 < h->chunk ? n - n0 : h->chunk);
-    const int ncb = (nc + 255) / 256 * 16;     // whole 256-cell tiles
+    const int ncb = (nc + 15) / 16;
     PropPrepArgs pa{x, ld, n0, nc, ncb, D, h->act[0], h->pc};
     e = launch_prop_prep(h->prec, pa, s);
     int cur = 0;
     for (int l = 0; l < h->L && e == hipSuccess; ++l) {
       LayerArgs la{(const uint8_t *)h->wpack[l], h->bias[l], h->act[cur], h->act[cur ^ 1],
-                   h->obuf, h->lR[l], h->lNQ[l], ncb, 16 * ncb, nullptr, 0, 0};
+                   h->obuf, h->lR[l], h->lNQ[l], ncb, 16 * ncb, h->lR[l], h->n_cu, nullptr, 0, 0};
       e = launch_layer(h->prec, la, l < h->L - 1, s);
       cur ^= 1;
     }

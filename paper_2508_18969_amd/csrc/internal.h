@@ -72,9 +72,11 @@ struct LayerArgs {
   const uint8_t *W;      // packed weights [R][NQ] fragments
   const float *bias;     // [16 R]
   const uint8_t *X;      // input B fragments [NQ][NCB]
-  uint8_t *Y;            // hidden layers: output B fragments [16 R / KS][NCB]
+  uint8_t *Y;            // hidden layers: output B fragments [16 RO / KS][NCB]
   float *O;              // output layer: FP32 [16 R][ldo]
   int R, NQ, NCB, ldo;   // row-blocks, input k-steps, cell-blocks of the chunk, O's stride
+  int RO;                // hidden layers: row-blocks written (R up to the next layer's k-steps)
+  int n_cu;              // compute units of the device
   // debug mode of hidden layers: FP32 accumulators of rows < dbg_rows and
   // cells < dbg_n into dbg_acc[row * dbg_n + cell]
   float *dbg_acc;

@@ -23,6 +23,8 @@
 // (cell cl, group g) holding input features frag_feature(KS, q, g, j); blocks
 // are ordered [q][cb], so the 16 cell-blocks of a tile are 16 consecutive
 // KiB.  Weights use the fused kernel's packed layout ([row-block][k-step]).
+#include <type_traits>
+
 #include "common.h"
 #include "internal.h"
 
@@ -31,7 +33,6 @@ namespace chemdnn {
 namespace {
 
 constexpr int FB = 64 * 16;        // bytes of one fragment (64 lanes x 16 bytes)
-constexpr int STAGES = 4;          // LDS k-step buffers in flight
 
 // Waits until at most N vector-memory operations of this wave are in flight.
 // Direct-to-LDS copies are not tracked by the compiler's own wait insertion;
@@ -52,123 +53,221 @@ __device__ __forceinline__ void wait_vmem_upto(int k) {
     else wait_vmem_upto<PER, MAXK - 1>(k);
   }
 }
-__device__ __forceinline__ void lds_barrier_all() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+// Every wave of the workgroup has finished its LDS reads (one wave: its own).
+template <int NW> __device__ __forceinline__ void stage_barrier() {
+  if constexpr (NW > 1) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 }
 
-// One wave copies the 1 KiB fragment at src (global) to dst (LDS), lane l's
-// 16 bytes to dst + 16 l, without passing through registers.
-__device__ __forceinline__ void dma_frag(const uint8_t *src, uint8_t *dst, int lane) {
-  __builtin_amdgcn_global_load_lds(
-      (const __attribute__((address_space(1))) void *)(src + (uint32_t)(lane * 16)),
-      (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
+// Fragments are copied through buffer resources: one per-lane offset and a
+// wave-uniform offset in an SGPR, no vector address arithmetic; reads past
+// the matrix return zero.
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+__device__ __forceinline__ rsrc_t layer_rsrc(const void *p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), (short)0, (int)bytes, 0x00020000);
 }
+// One wave copies the 1 KiB fragment at byte offset off to dst (LDS), lane
+// l's 16 bytes to dst + 16 l, without passing through registers.
+__device__ __forceinline__ void dma_frag(rsrc_t r, uint32_t off, uint8_t *dst, int lane) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)dst, 16,
+                                           lane * 16, (int)off, 0, 0);
+}
+
+// Calls f(U), f(U - 1), ..., f(1) with compile-time arguments.
+template <int U, class F> __device__ __forceinline__ void layer_tail(F &&f) {
+  if constexpr (U >= 1) {
+    f(std::integral_constant<int, U>{});
+    layer_tail<U - 1>(f);
+  }
+}
+
+// Tiles: rows x cells per workgroup, waves in a WR x WC grid of WRB x WCB
+// 16x16 blocks each, ST stages of KG k-steps.
+template <int WRB_, int WR_, int WCB_, int WC_, int ST_, int KG_> struct Tile {
+  static constexpr int WRB = WRB_, WR = WR_, WCB = WCB_, WC = WC_, ST = ST_, KG = KG_;
+  static constexpr int TRB = WRB * WR, TCB = WCB * WC, NT = 64 * WR * WC;
+  static constexpr int LDS = ST * KG * (TRB + TCB) * FB;
+  static_assert(LDS <= 160 * 1024, "LDS budget");
+};
+using T256 = Tile<4, 4, 8, 2, 4, 1>;   // 256 x 256, eight waves of 64 x 128
+using T128 = Tile<2, 4, 4, 2, 4, 1>;   // 128 x 128, eight waves of 32 x 64
+using T64 = Tile<2, 2, 2, 2, 4, 2>;    // 64 x 64, four waves of 32 x 32
+using T32 = Tile<2, 1, 2, 2, 4, 2>;    // 32 x 64, two waves of 32 x 32
+using T16 = Tile<2, 1, 1, 1, 8, 2>;    // 32 x 16, one wave
 
 }  // namespace
 
 // ------------------------------------------------------------------ layer
-// Workgroup tile: TRB = WRB*WR row-blocks x TCB = WCB*WC cell-blocks; eight
+// Workgroup tile: TRB = WRB*WR row-blocks x TCB = WCB*WC cell-blocks; NW = WR WC
 // waves in a WR x WC grid, each computing WRB x WCB 16x16 output blocks.  Per
-// k-step the tile's TRB weight fragments and TCB activation fragments are
-// copied to an LDS stage (every wave copies every eighth fragment); each wave
-// then reads its WRB + WCB fragments from LDS into registers one k-step ahead,
-// so that the reads of k-step q + 1 overlap the products of k-step q.  Four
-// stages: the copies of k-step q + 3 are issued once every wave has read the
-// fragments of k-step q (and so is done with the stage of q - 1).
+// stage (KG k-steps) the tile's weight and activation fragments are copied to
+// LDS (wave w copies the fragments w + NW k of each k-step); each wave then
+// reads its fragments from LDS into registers one stage ahead, between the
+// products of the current stage.  ST stages: the copies of stage t + ST - 1
+// are issued once every wave has read the fragments of stage t (and so is done
+// with the LDS space of stage t - 1).
+// Tiles may reach past the matrix: fragments past its last row- or cell-block
+// are read from the last one, and cell-blocks past NCB are not written;
+// row-blocks R .. RO - 1 (the rest of the next layer's last k-step) are
+// written as zeros.
 // DBG (hidden layers): the accumulators are also written to a.dbg_acc.
-template <class Op, int WRB, int WR, int WCB, int WC, bool ACT, bool DBG = false>
-__global__ __launch_bounds__(WR * WC * 64, 1) void layer_kernel(LayerArgs a) {
+//
+// Large chunks are bound by the matrix cores' power (a 256 x 256 tile's k-step
+// takes 580 ns alone and 870 ns with every CU busy; 1,024 cycles of products
+// against 768 of LDS reads); small ones by the k-step's chain of wait, barrier
+// and LDS read, and by how many CUs have a tile.  The steady loop has no
+// branches (constant waits, the copies' offsets in SGPRs), and its reads are
+// placed between the products: 4096 -> 2048 over 32,768 cells in BF16 takes
+// 450 us (1.22 PFLOP/s) against 518 with a branching loop whose products the
+// compiler had moved behind the next stage's barrier.
+template <class Op, class T, bool ACT, bool DBG = false>
+__global__ __launch_bounds__(T::NT, 1) void layer_kernel(LayerArgs a) {
+  constexpr int WRB = T::WRB, WR = T::WR, WCB = T::WCB, WC = T::WC, ST = T::ST, KG = T::KG;
   constexpr int NW = WR * WC;                         // waves
   static_assert(Op::FRAG == 16, "16-byte fragments");
   using frag_t = typename Op::frag_t;
-  constexpr int TRB = WRB * WR, TCB = WCB * WC, NF = TRB + TCB;
-  constexpr int PERW = NF % NW == 0 ? NF / NW : -1;  // copies per wave per k-step, if even
+  constexpr int TRB = T::TRB, TCB = T::TCB, NF = TRB + TCB;
+  static_assert(TRB % NW == 0 && TCB % NW == 0, "every wave copies as many fragments");
+  constexpr int PER = KG * NF / NW;                   // copies per wave per stage
+  static_assert(PER * (ST - 2) < 64, "copies in flight fit the wait counter");
+  constexpr int SB = KG * NF * FB;                    // bytes of a stage
   extern __shared__ __align__(16) uint8_t smem[];
   const int lane = threadIdx.x & 63, g = lane >> 4, cl = lane & 15;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wr = w % WR, wc = w / WR;
-  const int nrt = a.R / TRB;
+  const int nrt = (a.R + TRB - 1) / TRB;
   const int rt = blockIdx.x % nrt, ct = blockIdx.x / nrt;
   const int rb0 = rt * TRB, cb0 = ct * TCB;
-  const uint8_t *const Wt = a.W + (size_t)rb0 * a.NQ * FB;
-  const uint8_t *const Xt = a.X + (size_t)cb0 * FB;
 
-  // this wave's copies: fragments f = w + NW k of the NF of a k-step
-  auto issue = [&](int q, int s) {
-    uint8_t *dst = smem + s * NF * FB;
-    if constexpr (TRB % NW == 0 && TCB % NW == 0) {
+  // this wave's copies: fragments f = w + NW k of the NF of a k-step, as byte
+  // offsets at k-step 0 (weights advance by one fragment per k-step,
+  // activations by NCB fragments)
+  const rsrc_t Wr = layer_rsrc(a.W, (uint32_t)a.R * a.NQ * FB);
+  const rsrc_t Xr = layer_rsrc(a.X, (uint32_t)a.NQ * a.NCB * FB);
+  uint32_t wo[TRB / NW], xo[TCB / NW];
 #pragma unroll
-      for (int k = 0; k < NF / NW; ++k) {
-        const int f = w + NW * k;
-        const uint8_t *src = k < TRB / NW ? Wt + ((size_t)f * a.NQ + q) * FB
-                                          : Xt + ((size_t)q * a.NCB + (f - TRB)) * FB;
-        dma_frag(src, dst + f * FB, lane);
-      }
-    } else {
-      for (int f = w; f < NF; f += NW) {
-        const uint8_t *src = f < TRB ? Wt + ((size_t)f * a.NQ + q) * FB
-                                     : Xt + ((size_t)q * a.NCB + (f - TRB)) * FB;
-        dma_frag(src, dst + f * FB, lane);
-      }
+  for (int k = 0; k < TRB / NW; ++k) {
+    const int rb = rb0 + w + NW * k;
+    wo[k] = (uint32_t)((rb < a.R ? rb : a.R - 1) * a.NQ) * FB;
+  }
+#pragma unroll
+  for (int k = 0; k < TCB / NW; ++k) {
+    const int cb = cb0 + w + NW * k;
+    xo[k] = (uint32_t)(cb < a.NCB ? cb : a.NCB - 1) * FB;
+  }
+  const int N = (a.NQ + KG - 1) / KG;                 // stages
+  const uint32_t xstep = (uint32_t)a.NCB * FB;
+  // the next stage to copy: its k-step and LDS offset
+  int qi = 0, ws = 0;
+  auto issue = [&]() {
+#pragma unroll
+    for (int u = 0; u < KG; ++u) {
+      const uint32_t q = KG == 1 || qi + u < a.NQ ? qi + u : a.NQ - 1;
+      uint8_t *dst = smem + ws + (u * NF + w) * FB;
+#pragma unroll
+      for (int k = 0; k < TRB / NW; ++k) dma_frag(Wr, wo[k] + q * FB, dst + NW * k * FB, lane);
+#pragma unroll
+      for (int k = 0; k < TCB / NW; ++k) dma_frag(Xr, xo[k] + q * xstep, dst + (TRB + NW * k) * FB, lane);
     }
+    qi += KG;
+    ws = ws + SB == ST * SB ? 0 : ws + SB;
   };
-  auto read = [&](int q, frag_t (&af)[WRB], frag_t (&bf)[WCB]) {
-    const uint8_t *st = smem + (q % STAGES) * NF * FB + lane * 16;
-#pragma unroll
-    for (int i = 0; i < WRB; ++i) af[i] = *(const frag_t *)(st + (wr * WRB + i) * FB);
-#pragma unroll
-    for (int j = 0; j < WCB; ++j) bf[j] = *(const frag_t *)(st + (TRB + wc * WCB + j) * FB);
+  // the fragments of the next stage: part i of NP
+  constexpr int NP = KG * (WRB + WCB);
+  struct Regs { frag_t a[KG][WRB], b[KG][WCB]; };
+  Regs rg[2];
+  int rs = 0;                                         // LDS offset of the next stage to read
+  auto read = [&](Regs &d, const uint8_t *pa, const uint8_t *pb, int i) {
+    const int u = i / (WRB + WCB), k = i % (WRB + WCB);
+    if (k < WRB) d.a[u][k] = *(const frag_t *)(pa + (u * NF + k) * FB);
+    else d.b[u][k - WRB] = *(const frag_t *)(pb + (u * NF + k - WRB) * FB);
   };
 
   // accumulators start at the bias (rows 16 rb + 4 g + r)
   f4 acc[WRB][WCB];
 #pragma unroll
   for (int i = 0; i < WRB; ++i) {
-    const f4 b = *(const f4 *)(a.bias + 16 * (rb0 + wr * WRB + i) + 4 * g);
+    const int rb = rb0 + wr * WRB + i;
+    const f4 b = *(const f4 *)(a.bias + 16 * (rb < a.R ? rb : a.R - 1) + 4 * g);
 #pragma unroll
     for (int j = 0; j < WCB; ++j) acc[i][j] = b;
   }
 
-  // k-steps 0 .. STAGES - 2 in flight; k-step 0 in registers (the copies of
-  // the later ones may stay in flight)
-  for (int q = 0; q < STAGES - 1 && q < a.NQ; ++q) issue(q, q);
-  if constexpr (PERW > 0) {
-    const int issued = a.NQ < STAGES - 1 ? a.NQ : STAGES - 1;
-    wait_vmem_upto<PERW, STAGES - 2>(issued - 1);
-  } else {
-    wait_vmem<0>();
-  }
-  lds_barrier_all();
-  frag_t af[2][WRB], bf[2][WCB];
-  read(0, af[0], bf[0]);
-  for (int q = 0; q < a.NQ; q += 2) {
-    // two k-steps per trip, so the register buffers need no dynamic index
+  // one stage: with NEXT the fragments of the next stage are read between the
+  // products (WAIT: copies that may stay in flight then), with ISSUE the copies
+  // of stage + ST - 1 go out; `half`: the stage holds one k-step only
+  auto stage = [&](auto NEXT, auto ISSUE, auto WAIT, const Regs &cur, Regs &nxt, bool half) {
+    const uint8_t *pa = nullptr, *pb = nullptr;
+    if constexpr (NEXT()) {
+      wait_vmem<WAIT()>();
+      stage_barrier<NW>();
+      pa = smem + rs + wr * WRB * FB + lane * 16;
+      pb = smem + rs + (TRB + wc * WCB) * FB + lane * 16;
+      rs = rs + SB == ST * SB ? 0 : rs + SB;
+    }
+    if constexpr (ISSUE()) issue();
+    constexpr int NM = WRB * WCB, M = KG * NM;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int qq = q + h;
-      if (qq < a.NQ) {
-        if (qq + 1 < a.NQ) {
-          // k-step qq + 1: this wave's copies (those of qq + 2 .. qq +
-          // STAGES - 2 may be in flight), then every wave's; every wave has
-          // read k-step qq, so the stage of qq - 1 is free for k-step
-          // qq + STAGES - 1
-          if constexpr (PERW > 0) {
-            const int last = qq + STAGES - 2 < a.NQ - 1 ? qq + STAGES - 2 : a.NQ - 1;
-            wait_vmem_upto<PERW, STAGES - 3>(last - (qq + 1));
-          } else {
-            wait_vmem<0>();
-          }
-          lds_barrier_all();
-          if (qq + STAGES - 1 < a.NQ) issue(qq + STAGES - 1, (qq + STAGES - 1) % STAGES);
-          read(qq + 1, af[h ^ 1], bf[h ^ 1]);
-        }
+    for (int m = 0; m < M; ++m) {
+      if constexpr (NEXT()) {
 #pragma unroll
-        for (int i = 0; i < WRB; ++i)
+        for (int i = m * NP / M; i < (m + 1) * NP / M; ++i) read(nxt, pa, pb, i);
+      }
+      if (KG > 1 && m >= NM && half) continue;
+      const int u = m / NM, i = m % NM / WCB, j = m % WCB;
+      acc[i][j] = Op::mma(cur.a[u][i], cur.b[u][j], acc[i][j]);
+    }
+    // a read (or more) after each product, so that neither the matrix cores
+    // nor the LDS wait for the other's whole batch; nothing of the next stage
+    // moves up (its wait would come before these products)
+    if constexpr (NEXT()) {
 #pragma unroll
-          for (int j = 0; j < WCB; ++j) acc[i][j] = Op::mma(af[h][i], bf[h][j], acc[i][j]);
+      for (int m = 0; m < M; ++m) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, (NP + M - 1) / M, 0);
       }
     }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  using std::integral_constant;
+  constexpr std::true_type YES{};
+  constexpr std::false_type NO{};
+
+  // stages 0 .. ST - 2 in flight; stage 0 in registers
+  for (int t = 0; t < ST - 1 && t < N; ++t) issue();
+  {
+    const int issued = N < ST - 1 ? N : ST - 1;
+    wait_vmem_upto<PER, ST - 2>(issued - 1);
+    stage_barrier<NW>();
+    const uint8_t *pa = smem + wr * WRB * FB + lane * 16, *pb = smem + (TRB + wc * WCB) * FB + lane * 16;
+#pragma unroll
+    for (int i = 0; i < NP; ++i) read(rg[0], pa, pb, i);
+    rs = SB;
   }
+  integral_constant<int, PER * (ST - 3)> steady;
+  int t = 0;
+  // two stages per trip, so the register sets need no dynamic index
+  for (; t + ST < N; t += 2) {
+    stage(YES, YES, steady, rg[0], rg[1], false);
+    stage(YES, YES, steady, rg[1], rg[0], false);
+  }
+  if (t + ST - 1 < N) {
+    stage(YES, YES, steady, rg[0], rg[1], false);
+    rg[0] = rg[1];
+    ++t;
+  }
+  // the last rem <= ST - 1 stages: all their copies are out
+  const int rem = N - t;
+  if ((ST - 1 - rem) & 1) rg[1] = rg[0];
+  const bool half = KG > 1 && (a.NQ % KG) != 0;
+  layer_tail<ST - 1>([&](auto U) {
+    constexpr int u = U();                            // stages left, this one included
+    constexpr int s = (ST - 1 - u) & 1;
+    if (rem >= u) {
+      if constexpr (u > 1) stage(YES, NO, integral_constant<int, PER *(u - 2)>{}, rg[s], rg[s ^ 1], false);
+      else stage(NO, NO, integral_constant<int, 0>{}, rg[s], rg[s ^ 1], half);
+    }
+  });
 
   if constexpr (DBG) {
 #pragma unroll
@@ -190,18 +289,27 @@ __global__ __launch_bounds__(WR * WC * 64, 1) void layer_kernel(LayerArgs a) {
 #pragma unroll
     for (int i = 0; i < WRB; i += RPQ) {
       const int rb = rb0 + wr * WRB + i;
+      if (rb >= a.RO) continue;
 #pragma unroll
       for (int j = 0; j < WCB; ++j) {
         const int cb = cb0 + wc * WCB + j;
+        if (cb >= a.NCB) continue;
         __attribute__((aligned(16))) uint8_t buf[16];
 #pragma unroll
         for (int k = 0; k < RPQ; ++k) {
           f4 y;
 #pragma unroll
-          for (int r = 0; r < 4; ++r) y[r] = gelu(acc[i + k][j][r]);
+          for (int r = 0; r < 4; ++r) {
+            y[r] = gelu(acc[i + k][j][r]);
+            // an FP32 value before it is rounded to 16 bits, whatever the
+            // compiler could fuse (v_fma_mix rounds the last product once)
+            asm("" : "+v"(y[r]));
+          }
           Op::store4(buf + 4 * k * Op::EB, y);
         }
-        *(i4 *)(a.Y + ((size_t)(rb / RPQ) * a.NCB + cb) * FB + lane * 16) = *(const i4 *)buf;
+        i4 v = *(const i4 *)buf;
+        if (RPQ == 2 && rb + 1 >= a.R) v[2] = v[3] = 0;
+        *(i4 *)(a.Y + ((size_t)(rb / RPQ) * a.NCB + cb) * FB + lane * 16) = v;
       }
     }
   } else {
@@ -209,11 +317,13 @@ __global__ __launch_bounds__(WR * WC * 64, 1) void layer_kernel(LayerArgs a) {
 #pragma unroll
     for (int i = 0; i < WRB; ++i)
 #pragma unroll
-      for (int j = 0; j < WCB; ++j)
+      for (int j = 0; j < WCB; ++j) {
+        const int rb = rb0 + wr * WRB + i, cb = cb0 + wc * WCB + j;
+        if (rb >= a.R || cb >= a.NCB) continue;
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          a.O[(size_t)(16 * (rb0 + wr * WRB + i) + 4 * g + r) * a.ldo + 16 * (cb0 + wc * WCB + j) + cl] =
-              acc[i][j][r];
+          a.O[(size_t)(16 * rb + 4 * g + r) * a.ldo + 16 * cb + cl] = acc[i][j][r];
+      }
   }
 }
 
@@ -389,37 +499,66 @@ hipError_t set_lds(K kern, int bytes) {
   return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
-// hidden layers: 256 x 256 tiles (16 row-blocks x 16 cell-blocks) over
-// HWR x HWC waves of HWRB x HWCB blocks each
-constexpr int HWRB = 4, HWR = 4, HWCB = 8, HWC = 2;
-static_assert(HWRB * HWR == 16 && HWCB * HWC == 16, "256 x 256 tiles");
-constexpr int LDS_HIDDEN = STAGES * (16 + 16) * FB;
-constexpr int LDS_OUT = STAGES * (2 + 16) * FB;
-static_assert(LDS_HIDDEN <= 160 * 1024, "LDS budget");
-
-template <class Op>
-hipError_t launch_layer_op(const LayerArgs &a, bool hidden, hipStream_t s) {
-  if (hidden) {
-    auto k = layer_kernel<Op, HWRB, HWR, HWCB, HWC, true>;
-    const int grid = (a.R / 16) * (a.NCB / 16);
-    constexpr int LDS = LDS_HIDDEN, NT = 64 * HWR * HWC;
-    hipLaunchKernelGGL(k, dim3(grid), dim3(NT), LDS, s, a);
-  } else {
-    // output layer, 32 rows: 2 row-blocks x 16 cell-blocks (2 per wave)
-    constexpr int LDS = LDS_OUT;
-    auto k = layer_kernel<Op, 2, 1, 2, 8, false>;
-    const int grid = (a.R / 2) * (a.NCB / 16);
-    hipLaunchKernelGGL(k, dim3(grid), dim3(512), LDS, s, a);
-  }
+template <class Op, class T, bool ACT, bool DBG = false>
+hipError_t launch_tile(const LayerArgs &a, hipStream_t s) {
+  auto k = layer_kernel<Op, T, ACT, DBG>;
+  const int grid = ((a.R + T::TRB - 1) / T::TRB) * ((a.NCB + T::TCB - 1) / T::TCB);
+  hipLaunchKernelGGL(k, dim3(grid), dim3(T::NT), T::LDS, s, a);
   return hipGetLastError();
 }
 
+// The tile of a hidden layer.  A launch of G workgroups puts c = ceil(G / CUs)
+// of them on the fullest CU; a k-step then takes about max(lat, c thr) ns,
+// where lat is a lone workgroup's k-step (waits, barrier and the products of
+// one wave) and thr its share of a full CU (products, LDS and L2 reads).
+// Measured on the layers of 19-2048-4096-2048-1024-512-17 at 16 to 32,768 cells
+// (lat from 16 cells, thr from the largest sizes of each tile).  The small
+// tiles fill the chip for small chunks, the large ones read each operand
+// fewer times: at 1,000 cells the 4096 -> 2048 layer takes 77 us on 32
+// workgroups of 256 x 256 and 26 us on 512 of 64 x 64; at 32,768 cells 450 us
+// against 940 us.
+struct TileCost { int trb, tcb, lat, thr; };
+constexpr TileCost kCost16[5] = {{T256::TRB, T256::TCB, 580, 870}, {T128::TRB, T128::TCB, 210, 270},
+                                 {T64::TRB, T64::TCB, 96, 92}, {T32::TRB, T32::TCB, 94, 70},
+                                 {T16::TRB, T16::TCB, 77, 50}};
+constexpr TileCost kCost32[5] = {{T256::TRB, T256::TCB, 3540, 3540}, {T128::TRB, T128::TCB, 920, 910},
+                                 {T64::TRB, T64::TCB, 280, 245}, {T32::TRB, T32::TCB, 275, 230},
+                                 {T16::TRB, T16::TCB, 165, 110}};
+int pick_tile(const TileCost (&cost)[5], const LayerArgs &a) {
+  int best = 0;
+  int64_t tb = INT64_MAX;
+  for (int k = 0; k < 5; ++k) {
+    const int64_t G = (int64_t)((a.R + cost[k].trb - 1) / cost[k].trb) *
+                      ((a.NCB + cost[k].tcb - 1) / cost[k].tcb);
+    const int64_t c = (G + a.n_cu - 1) / a.n_cu, t = c * cost[k].thr;
+    const int64_t u = t > cost[k].lat ? t : cost[k].lat;
+    if (u < tb) tb = u, best = k;
+  }
+  return best;
+}
+
+template <class Op>
+hipError_t launch_layer_op(const LayerArgs &a, bool hidden, hipStream_t s) {
+  if (!hidden) return launch_tile<Op, T32, false>(a, s);
+  switch (pick_tile(Op::EB == 4 ? kCost32 : kCost16, a)) {
+    case 0: return launch_tile<Op, T256, true>(a, s);
+    case 1: return launch_tile<Op, T128, true>(a, s);
+    case 2: return launch_tile<Op, T64, true>(a, s);
+    case 3: return launch_tile<Op, T32, true>(a, s);
+    default: return launch_tile<Op, T16, true>(a, s);
+  }
+}
+
+// the layer dump: the same tiles with the accumulators written out
 template <class Op>
 hipError_t launch_layer_dbg_op(const LayerArgs &a, hipStream_t s) {
-  auto k = layer_kernel<Op, HWRB, HWR, HWCB, HWC, true, true>;
-  const int grid = (a.R / 16) * (a.NCB / 16);
-  hipLaunchKernelGGL(k, dim3(grid), dim3(64 * HWR * HWC), LDS_HIDDEN, s, a);
-  return hipGetLastError();
+  switch (pick_tile(Op::EB == 4 ? kCost32 : kCost16, a)) {
+    case 0: return launch_tile<Op, T256, true, true>(a, s);
+    case 1: return launch_tile<Op, T128, true, true>(a, s);
+    case 2: return launch_tile<Op, T64, true, true>(a, s);
+    case 3: return launch_tile<Op, T32, true, true>(a, s);
+    default: return launch_tile<Op, T16, true, true>(a, s);
+  }
 }
 
 }  // namespace
@@ -456,16 +595,19 @@ hipError_t launch_copy_rows(const float *src, int ld_src, int rows, int n, float
 }
 
 // The layer kernels use more than the default 64 KiB of LDS.
+template <class Op, class T, bool ACT, bool DBG = false> static hipError_t prepare_tile() {
+  return set_lds(layer_kernel<Op, T, ACT, DBG>, T::LDS);
+}
+template <class Op> static hipError_t prepare_op() {
+  hipError_t e = prepare_tile<Op, T256, true>();   // (the other tiles: at most 64 KiB)
+  if (e == hipSuccess) e = prepare_tile<Op, T256, true, true>();
+  static_assert(T128::LDS <= 65536 && T64::LDS <= 65536 && T32::LDS <= 65536 && T16::LDS <= 65536, "LDS");
+  return e;
+}
 hipError_t layered_prepare() {
-  hipError_t e = set_lds(layer_kernel<OpF32, HWRB, HWR, HWCB, HWC, true>, LDS_HIDDEN);
-  if (e == hipSuccess) e = set_lds(layer_kernel<OpF32, HWRB, HWR, HWCB, HWC, true, true>, LDS_HIDDEN);
-  if (e == hipSuccess) e = set_lds(layer_kernel<OpBF16, HWRB, HWR, HWCB, HWC, true, true>, LDS_HIDDEN);
-  if (e == hipSuccess) e = set_lds(layer_kernel<OpF16, HWRB, HWR, HWCB, HWC, true, true>, LDS_HIDDEN);
-  if (e == hipSuccess) e = set_lds(layer_kernel<OpBF16, HWRB, HWR, HWCB, HWC, true>, LDS_HIDDEN);
-  if (e == hipSuccess) e = set_lds(layer_kernel<OpF16, HWRB, HWR, HWCB, HWC, true>, LDS_HIDDEN);
-  if (e == hipSuccess) e = set_lds(layer_kernel<OpF32, 2, 1, 2, 8, false>, LDS_OUT);
-  if (e == hipSuccess) e = set_lds(layer_kernel<OpBF16, 2, 1, 2, 8, false>, LDS_OUT);
-  if (e == hipSuccess) e = set_lds(layer_kernel<OpF16, 2, 1, 2, 8, false>, LDS_OUT);
+  hipError_t e = prepare_op<OpF32>();
+  if (e == hipSuccess) e = prepare_op<OpBF16>();
+  if (e == hipSuccess) e = prepare_op<OpF16>();
   return e;
 }
 
