@@ -22,7 +22,6 @@ struct chem_dnn {
   int layered;
   int lR[8], lNQ[8];   // per layer: output row-blocks, input k-steps
   uint8_t *act[2];     // activation fragment buffers of one chunk
-  float *obuf;         // FP32 network output of one chunk [32][chunk]
   int dev, n_cu;
   uint8_t *ws;
   size_t ws_bytes;
@@ -61,7 +60,6 @@ struct chem_prop {
   float *bias[8];
   void *wpack[8];
   uint8_t *act[2];       // activation fragment buffers of one chunk
-  float *obuf;           // FP32 network output of one chunk [32][chunk]
   double hpc[PConst::N]; // host copies kept alive for the asynchronous uploads
   float hfc[FConst::N];
 };
@@ -128,7 +126,7 @@ int32_t hip_status(hipError_t e) { return e == hipSuccess ? CHEM_DNN_OK : CHEM_D
 
 // Offsets of every sub-buffer inside the workspace.
 struct WsPlan {
-  size_t fc, dc, amax, gtab, bias[8], w[8], act[2], obuf, train, total;
+  size_t fc, dc, amax, gtab, bias[8], w[8], act[2], train, total;
 };
 
 // Layer-by-layer path: cells per chunk (activation buffers are sized for it).
@@ -198,7 +196,7 @@ int32_t plan(const chem_dnn_desc *d, NetLayout *lay, WsPlan *p) {
       p->w[l] = off;
       off = align_up(off + (size_t)lay->R[l] * 16 * lay->NQ[l] * lay->KS * lay->EB);
     }
-    p->act[0] = p->act[1] = p->obuf = 0;
+    p->act[0] = p->act[1] = 0;
   } else {
     const int ks = ks_of(d->precision), eb = eb_of(d->precision);
     int kmax = 32;
@@ -215,8 +213,6 @@ int32_t plan(const chem_dnn_desc *d, NetLayout *lay, WsPlan *p) {
       p->act[b] = off;
       off = align_up(off + (size_t)kmax * kChunk * eb);
     }
-    p->obuf = off;
-    off = align_up(off + (size_t)32 * kChunk * sizeof(float));
   }
   p->train = off;
   off += fused ? train_scratch_bytes(d->widths, d->max_batch, d->recompute_chunk) : 0;
@@ -262,13 +258,14 @@ int32_t pack_params(chem_dnn *h, const float *params, hipStream_t s) {
   if (e == hipSuccess) e = launch_pow2_scales(h->amax_bits, h->fc, 4, fp8 ? 1 : 0, s);
   static const int fmt_of[4] = {0, 1, 2, 3};
   if (h->layered) {
-    // output rows unshifted; the w_scale operand is read for FP8 only
+    // output rows shifted by two, as the post-processing takes them; the
+    // w_scale operand is read for FP8 only
     for (int l = 0; l < h->L && e == hipSuccess; ++l) {
-      const int N = h->widths[l + 1], K = h->widths[l];
-      e = launch_pack(params + param_offset(h->widths, l, false), N, K, 0, h->lR[l], h->lNQ[l],
+      const int N = h->widths[l + 1], K = h->widths[l], rowshift = l == h->L - 1 ? 2 : 0;
+      e = launch_pack(params + param_offset(h->widths, l, false), N, K, rowshift, h->lR[l], h->lNQ[l],
                       ks_of(h->prec), fmt_of[h->prec], h->fc + FConst::WSCALE, h->wpack[l], s);
       if (e == hipSuccess)
-        e = launch_pad_bias(params + param_offset(h->widths, l, true), N, 0, h->lR[l] * 16,
+        e = launch_pad_bias(params + param_offset(h->widths, l, true), N, rowshift, h->lR[l] * 16,
                             h->bias[l], s);
     }
     return hip_status(e);
@@ -303,34 +300,35 @@ StepArgs step_args(chem_dnn *h, int64_t n, int64_t ld, const double *T, const do
   return a;
 }
 
-// The layer-by-layer path over chunks of kChunk cells: preprocess, one
-// launch per layer, post-processing.
+// The layer-by-layer path over chunks of kChunk cells: the first layer with
+// the input transform, one launch per further hidden layer, the output layer
+// with the post-processing.
 int32_t run_layered(chem_dnn *h, int64_t n, int64_t ld, const double *T, const double *P,
                     const double *Y, double *Y_out, double *T_out, double *omega, double inv_dt,
                     uint32_t *n_bad, hipStream_t s) {
-  const int fmt = h->prec;   // 0 FP32, 1 BF16, 2 FP16
+  const int fmt = h->prec, L = h->L;   // 0 FP32, 1 BF16, 2 FP16
   // the chunk buffers lie inside the workspace
   const uint8_t *end = h->ws + h->ws_bytes;
-  if (h->act[0] < h->ws || h->act[1] < h->ws || (const uint8_t *)h->obuf < h->ws ||
-      (const uint8_t *)(h->obuf + 32 * kChunk) > end)
-    return CHEM_DNN_EWORKSPACE;
+  if (h->act[0] < h->ws || h->act[1] < h->act[0] || h->act[1] > end) return CHEM_DNN_EWORKSPACE;
   hipError_t e = hipSuccess;
   for (int64_t n0 = 0; n0 < n && e == hipSuccess; n0 += kChunk) {
     const int nc = (int)(n - n0 < kChunk ? n - n0 : kChunk);
     const int ncb = (nc + 15) / 16;
-    PrepArgs pa{T, P, Y, ld, n0, nc, ncb, h->act[0], h->fc, h->dc, h->S};
-    e = launch_prep(fmt, pa, s);
+    FirstArgs fa{T, P, Y, ld, n0, nc, ncb, h->D, (const uint8_t *)h->wpack[0], h->bias[0], h->act[0],
+                 h->lR[0], h->lR[0], h->fc, h->dc, h->n_cu, 0, nullptr, nullptr, 0};
+    e = launch_first(fmt, fa, false, false, s);
     int cur = 0;
-    for (int l = 0; l < h->L && e == hipSuccess; ++l) {
-      LayerArgs la{h->wpack[l] ? (const uint8_t *)h->wpack[l] : nullptr, h->bias[l], h->act[cur],
-                   h->act[cur ^ 1], h->obuf, h->lR[l], h->lNQ[l], ncb, 16 * ncb, h->lR[l], h->n_cu, nullptr, 0, 0};
-      e = launch_layer(fmt, la, l < h->L - 1, s);
+    for (int l = 1; l < L - 1 && e == hipSuccess; ++l) {
+      LayerArgs la{(const uint8_t *)h->wpack[l], h->bias[l], h->act[cur], h->act[cur ^ 1], h->lR[l],
+                   h->lNQ[l], ncb, h->lR[l], h->n_cu, nullptr, 0, 0};
+      e = launch_layer(fmt, la, s);
       cur ^= 1;
     }
     if (e == hipSuccess) {
-      PostArgs po{T, P, Y, Y_out, T_out, omega, n_bad, ld, n0, nc, 16 * ncb, h->obuf, h->fc,
-                  h->dc, inv_dt, h->S, h->thermo};
-      e = launch_post(po, s);
+      LastArgs ea{T, P, Y, Y_out, T_out, omega, n_bad, ld, n0, nc, ncb, h->S,
+                  (const uint8_t *)h->wpack[L - 1], h->bias[L - 1], h->act[cur], h->lNQ[L - 1],
+                  h->fc, h->dc, inv_dt, h->thermo, nullptr};
+      e = launch_last(fmt, ea, false, false, s);
     }
   }
   return hip_status(e);
@@ -373,7 +371,7 @@ int64_t prop_chunk(const chem_prop_desc *d) {
 }
 
 struct PropPlan {
-  size_t pc, fc, bias[8], w[8], act[2], obuf, total;
+  size_t pc, fc, bias[8], w[8], act[2], total;
   int64_t chunk;
   bool fused;
   NetLayout lay;
@@ -398,7 +396,7 @@ int32_t prop_plan(const chem_prop_desc *d, PropPlan *p) {
       p->w[l] = off;
       off = align_up(off + (size_t)p->lay.R[l] * 16 * p->lay.NQ[l] * p->lay.KS * p->lay.EB);
     }
-    p->act[0] = p->act[1] = p->obuf = 0;
+    p->act[0] = p->act[1] = 0;
     p->total = off;
     return CHEM_DNN_OK;
   }
@@ -416,8 +414,6 @@ int32_t prop_plan(const chem_prop_desc *d, PropPlan *p) {
     p->act[b] = off;
     off = align_up(off + (size_t)kmax * p->chunk * eb);
   }
-  p->obuf = off;
-  off = align_up(off + (size_t)32 * p->chunk * sizeof(float));
   p->total = off;
   return CHEM_DNN_OK;
 }
@@ -535,7 +531,6 @@ int32_t chem_dnn_init(const chem_dnn_desc *d, const float *params, void *workspa
     // (workspace pointers: only once h->ws is set)
     h->act[0] = h->ws + p.act[0];
     h->act[1] = h->ws + p.act[1];
-    h->obuf = (float *)(h->ws + p.obuf);
   }
   h->fc = (float *)(h->ws + p.fc);
   h->gtab = (float *)(h->ws + p.gtab);
@@ -774,28 +769,26 @@ int32_t chem_dnn_debug_layers(chem_dnn *h, int64_t n, int64_t ld, const double *
     return hip_status(h->lay.dbg(a, grid_for(h, a.ntiles), s));
   }
   // layer by layer: one chunk (n <= CHEM_DNN_DEBUG_MAX_CELLS < kChunk)
-  const int fmt = h->prec;
+  const int fmt = h->prec, L = h->L;
   const int nc = (int)n, ncb = (nc + 15) / 16;
-  PrepArgs pa{T, P, Y, ld, 0, nc, ncb, h->act[0], h->fc, h->dc, h->S};
-  hipError_t e = launch_prep(fmt, pa, s);
-  if (e == hipSuccess) e = launch_frag_decode(fmt, h->act[0], ncb, h->widths[0], nc, qin, s);
+  FirstArgs fa{T, P, Y, ld, 0, nc, ncb, h->D, (const uint8_t *)h->wpack[0], h->bias[0], h->act[0],
+               h->lR[0], h->lR[0], h->fc, h->dc, h->n_cu, 0, qin, acc, h->widths[1]};
+  hipError_t e = launch_first(fmt, fa, false, true, s);
   int cur = 0;
-  for (int l = 0; l < h->L && e == hipSuccess; ++l) {
-    const bool hidden = l < h->L - 1;
-    LayerArgs la{(const uint8_t *)h->wpack[l], h->bias[l], h->act[cur], h->act[cur ^ 1], h->obuf,
-                 h->lR[l], h->lNQ[l], ncb, 16 * ncb, h->lR[l], h->n_cu, nullptr, 0, 0};
-    if (hidden) {
-      la.dbg_acc = acc + (size_t)acc_row[l] * nc;
-      la.dbg_rows = h->widths[l + 1];
-      la.dbg_n = nc;
+  for (int l = 1; l < L && e == hipSuccess; ++l) {
+    // layer l's input, then the layer
+    e = launch_frag_decode(fmt, h->act[cur], ncb, h->widths[l], nc, qin + (size_t)in_row[l] * nc, s);
+    if (e != hipSuccess) break;
+    float *const la_acc = acc + (size_t)acc_row[l] * nc;
+    if (l < L - 1) {
+      LayerArgs la{(const uint8_t *)h->wpack[l], h->bias[l], h->act[cur], h->act[cur ^ 1], h->lR[l],
+                   h->lNQ[l], ncb, h->lR[l], h->n_cu, la_acc, h->widths[l + 1], nc};
       e = launch_layer_dbg(fmt, la, s);
-      if (e == hipSuccess)
-        e = launch_frag_decode(fmt, h->act[cur ^ 1], ncb, h->widths[l + 1], nc,
-                               qin + (size_t)in_row[l + 1] * nc, s);
     } else {
-      e = launch_layer(fmt, la, false, s);
-      if (e == hipSuccess)
-        e = launch_copy_rows(h->obuf, 16 * ncb, h->S, nc, acc + (size_t)acc_row[l] * nc, s);
+      LastArgs ea{T, P, Y, nullptr, nullptr, nullptr, nullptr, ld, 0, nc, ncb, h->S,
+                  (const uint8_t *)h->wpack[l], h->bias[l], h->act[cur], h->lNQ[l], h->fc, h->dc,
+                  0.0, 0, la_acc};
+      e = launch_last(fmt, ea, false, true, s);
     }
     cur ^= 1;
   }
@@ -850,7 +843,6 @@ int32_t chem_prop_init(const chem_prop_desc *d, const float *params, void *works
   if (!h->fused) {
     h->act[0] = h->ws + p.act[0];
     h->act[1] = h->ws + p.act[1];
-    h->obuf = (float *)(h->ws + p.obuf);
   }
   memset(h->hfc, 0, sizeof(h->hfc));
   for (int l = 0; l < 4; ++l) {
@@ -913,24 +905,26 @@ int32_t chem_prop_eval(chem_prop *h, int64_t n, int64_t ld, const double *x, dou
     const int64_t grid = a.ntiles < h->n_cu ? a.ntiles : h->n_cu;
     return hip_status(h->lay.step(a, (int)(grid < 1 ? 1 : grid), s));
   }
-  const uint8_t *end = h->ws + h->ws_bytes;
-  if ((const uint8_t *)(h->obuf + 32 * h->chunk) > end) return CHEM_DNN_EWORKSPACE;
+  const int L = h->L;
   hipError_t e = hipSuccess;
   for (int64_t n0 = 0; n0 < n && e == hipSuccess; n0 += h->chunk) {
     const int nc = (int)(n - n0 < h->chunk ? n - n0 : h->chunk);
     const int ncb = (nc + 15) / 16;
-    PropPrepArgs pa{x, ld, n0, nc, ncb, D, h->act[0], h->pc};
-    e = launch_prop_prep(h->prec, pa, s);
+    FirstArgs fa{nullptr, nullptr, x, ld, n0, nc, ncb, D, (const uint8_t *)h->wpack[0], h->bias[0],
+                 h->act[0], h->lR[0], h->lR[0], nullptr, h->pc, h->n_cu, 0, nullptr, nullptr, 0};
+    e = launch_first(h->prec, fa, true, false, s);
     int cur = 0;
-    for (int l = 0; l < h->L && e == hipSuccess; ++l) {
-      LayerArgs la{(const uint8_t *)h->wpack[l], h->bias[l], h->act[cur], h->act[cur ^ 1],
-                   h->obuf, h->lR[l], h->lNQ[l], ncb, 16 * ncb, h->lR[l], h->n_cu, nullptr, 0, 0};
-      e = launch_layer(h->prec, la, l < h->L - 1, s);
+    for (int l = 1; l < L - 1 && e == hipSuccess; ++l) {
+      LayerArgs la{(const uint8_t *)h->wpack[l], h->bias[l], h->act[cur], h->act[cur ^ 1], h->lR[l],
+                   h->lNQ[l], ncb, h->lR[l], h->n_cu, nullptr, 0, 0};
+      e = launch_layer(h->prec, la, s);
       cur ^= 1;
     }
     if (e == hipSuccess) {
-      PropPostArgs po{y, ld, n0, nc, K, 16 * ncb, h->obuf, h->pc};
-      e = launch_prop_post(po, s);
+      LastArgs ea{nullptr, nullptr, nullptr, y, nullptr, nullptr, nullptr, ld, n0, nc, ncb, K,
+                  (const uint8_t *)h->wpack[L - 1], h->bias[L - 1], h->act[cur], h->lNQ[L - 1],
+                  nullptr, h->pc, 0.0, 0, nullptr};
+      e = launch_last(h->prec, ea, true, false, s);
     }
   }
   return hip_status(e);

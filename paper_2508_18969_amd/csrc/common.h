@@ -194,6 +194,18 @@ __device__ __forceinline__ uint32_t quad_or(uint32_t v) {
   return b[0] | b[1];
 }
 
+// v rounded to FP32 towards the odd neighbour when inexact: rounding the
+// result to a 16-bit format is then the same as rounding v itself once.
+__device__ __forceinline__ float to_odd(double v) {
+  const float f = (float)v;
+  const double b = (double)f;
+  uint32_t u = __builtin_bit_cast(uint32_t, f);
+  const bool inexact = b < v || b > v;         // (false for NaN)
+  const uint32_t step = __builtin_fabs(b) < __builtin_fabs(v) ? 1u : ~0u;
+  u += inexact && !(u & 1u) ? step : 0u;
+  return __builtin_bit_cast(float, u);
+}
+
 // ---------------------------------------------------------------- operand formats
 // KS: input features per k-step; FRAG: bytes per lane per fragment;
 // EB: bytes per element; SCALED: operands carry power-of-two scales.
@@ -213,6 +225,11 @@ struct OpF32 {
   static __device__ __forceinline__ void store4(uint8_t *p, f4 v) { *(f4 *)p = v; }
   // the operand value a stored v becomes, as FP32
   static __device__ __forceinline__ float q(float v) { return v; }
+  // one input feature: v, or fma(u, za, zc)
+  static __device__ __forceinline__ float feature(double v) { return (float)v; }
+  static __device__ __forceinline__ float feature(float u, float za, float zc) {
+    return __builtin_fmaf(u, za, zc);
+  }
   static __device__ __forceinline__ void store4s(uint8_t *p, f4 v, float) { store4(p, v); }
 };
 
@@ -231,6 +248,11 @@ struct OpBF16 {
     *(b4 *)p = o;
   }
   static __device__ __forceinline__ float q(float v) { return (float)(__bf16)v; }
+  // one input feature: v, or fma(u, za, zc)
+  static __device__ __forceinline__ __bf16 feature(double v) { return (__bf16)to_odd(v); }
+  static __device__ __forceinline__ __bf16 feature(float u, float za, float zc) {
+    return (__bf16)__builtin_fmaf(u, za, zc);
+  }
   static __device__ __forceinline__ void store4s(uint8_t *p, f4 v, float) { store4(p, v); }
 };
 
@@ -249,6 +271,14 @@ struct OpF16 {
     *(q4 *)p = o;
   }
   static __device__ __forceinline__ float q(float v) { return (float)(_Float16)v; }
+  // one input feature: v, or fma(u, za, zc) rounded once, to 16 bits (no FP32
+  // value in between)
+  static __device__ __forceinline__ _Float16 feature(double v) { return (_Float16)to_odd(v); }
+  static __device__ __forceinline__ _Float16 feature(float u, float za, float zc) {
+    uint32_t m;
+    asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[0,0,0]" : "=v"(m) : "v"(u), "v"(za), "v"(zc));
+    return __builtin_bit_cast(_Float16, (uint16_t)m);
+  }
   static __device__ __forceinline__ void store4s(uint8_t *p, f4 v, float) { store4(p, v); }
 };
 
@@ -291,6 +321,14 @@ struct OpF8 {
     return __builtin_amdgcn_cvt_f32_fp8((int)w, 0);
   }
 };
+
+// A copy of a per-lane value that the optimisers can not see through: LDS
+// addresses built on it keep their constant parts in the instruction's offset
+// field.
+__device__ __forceinline__ int opaque_v(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
 
 template <int A, int B> struct Max { static constexpr int v = A > B ? A : B; };
 constexpr int roundup(int x, int m) { return (x + m - 1) / m * m; }

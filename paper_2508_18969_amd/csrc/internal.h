@@ -68,40 +68,56 @@ constexpr int GTAB_N = 600;
 constexpr float GTAB_LO = -3.0f, GTAB_HI = 3.0f, GTAB_INV_H = 100.0f, GTAB_H = 0.01f;
 
 // Layer-by-layer path (layered.hip): arguments of its three kernels.
+// Hidden layer.
 struct LayerArgs {
   const uint8_t *W;      // packed weights [R][NQ] fragments
   const float *bias;     // [16 R]
   const uint8_t *X;      // input B fragments [NQ][NCB]
-  uint8_t *Y;            // hidden layers: output B fragments [16 RO / KS][NCB]
-  float *O;              // output layer: FP32 [16 R][ldo]
-  int R, NQ, NCB, ldo;   // row-blocks, input k-steps, cell-blocks of the chunk, O's stride
-  int RO;                // hidden layers: row-blocks written (R up to the next layer's k-steps)
+  uint8_t *Y;            // output B fragments [16 RO / KS][NCB]
+  int R, NQ, NCB;        // row-blocks, input k-steps, cell-blocks of the chunk
+  int RO;                // row-blocks written (R up to the next layer's k-steps)
   int n_cu;              // compute units of the device
-  // debug mode of hidden layers: FP32 accumulators of rows < dbg_rows and
-  // cells < dbg_n into dbg_acc[row * dbg_n + cell]
+  // debug mode: FP32 accumulators of rows < dbg_rows and cells < dbg_n into
+  // dbg_acc[row * dbg_n + cell]
   float *dbg_acc;
   int dbg_rows, dbg_n;
 };
-struct PrepArgs {
-  const double *T, *P, *Y;
+// First hidden layer with the input transform.
+struct FirstArgs {
+  const double *T, *P;   // chemistry networks: temperature and pressure
+  const double *x;       // mass fractions [D - 2][ld], or the property inputs [D][ld]
   int64_t ld, n0;        // field stride; first cell of the chunk
-  int nc, NCB;           // cells of the chunk; cell-blocks written (>= nc / 16)
-  uint8_t *X;            // layer-1 B fragments [32 / KS][NCB]
-  const float *fc;
-  const double *dc;
-  int S;
+  int nc, NCB, D;        // cells of the chunk; cell-blocks written; inputs
+  const uint8_t *W;      // packed weights [R][32 / KS] fragments
+  const float *bias;     // [16 R]
+  uint8_t *Y;            // output B fragments [16 RO / KS][NCB]
+  int R, RO;             // row-blocks; row-blocks written
+  const float *fc;       // FConst block
+  const double *dc;      // DConst block (property networks: PConst)
+  int n_cu;              // compute units of the device
+  int RPW;               // row-blocks per wave (set by the launcher)
+  // debug mode: input operand values [D][nc] and accumulators [dbg_rows][nc]
+  float *dbg_in, *dbg_acc;
+  int dbg_rows;
 };
-struct PostArgs {
-  const double *T, *P, *Y;
-  double *Y_out, *T_out, *omega;
+// Output layer with the post-processing.
+struct LastArgs {
+  const double *T, *P;   // chemistry networks
+  const double *x;       // mass fractions [S][ld]
+  double *Y_out;         // new mass fractions, or the property outputs, [S][ld]
+  double *T_out, *omega;
   uint32_t *n_bad;
   int64_t ld, n0;
-  int nc, ldo;
-  const float *O;        // network output [S][ldo] of the chunk
+  int nc, NCB, S;        // cells and cell-blocks of the chunk; species, or property outputs
+  const uint8_t *W;      // packed weights [2][NQ] fragments (chemistry: rows shifted by two)
+  const float *bias;     // [32]
+  const uint8_t *X;      // input B fragments [NQ][NCB]
+  int NQ;
   const float *fc;
   const double *dc;
   double inv_dt;
-  int S, thermo;
+  int thermo;
+  float *dbg_acc;        // debug mode: accumulators [S][nc]
 };
 // Property networks: FP64 constants of the input and output affine maps.
 struct PConst {
@@ -113,34 +129,16 @@ struct PConst {
     N = 128
   };
 };
-struct PropPrepArgs {
-  const double *x;       // input fields [D][ld]
-  int64_t ld, n0;        // field stride; first cell of the chunk
-  int nc, NCB, D;        // cells of the chunk; cell-blocks written; input count
-  uint8_t *X;            // layer-1 B fragments [32 / KS][NCB]
-  const double *pc;      // PConst block
-};
-struct PropPostArgs {
-  double *y;             // outputs [K][ld]
-  int64_t ld, n0;
-  int nc, K, ldo;        // cells of the chunk; outputs; O's stride
-  const float *O;        // network output [K][ldo] of the chunk
-  const double *pc;
-};
-// fmt: 0 FP32, 1 BF16, 2 FP16 operands
+// fmt: 0 FP32, 1 BF16, 2 FP16 operands; prop: property network; dbg: layer dump
 hipError_t layered_prepare();
-hipError_t launch_prep(int fmt, const PrepArgs &a, hipStream_t s);
-hipError_t launch_layer(int fmt, const LayerArgs &a, bool hidden, hipStream_t s);
-hipError_t launch_post(const PostArgs &a, hipStream_t s);
-hipError_t launch_prop_prep(int fmt, const PropPrepArgs &a, hipStream_t s);
-hipError_t launch_prop_post(const PropPostArgs &a, hipStream_t s);
+hipError_t launch_first(int fmt, const FirstArgs &a, bool prop, bool dbg, hipStream_t s);
+hipError_t launch_layer(int fmt, const LayerArgs &a, hipStream_t s);
+hipError_t launch_last(int fmt, const LastArgs &a, bool prop, bool dbg, hipStream_t s);
 // debug: hidden layer with its accumulators dumped; the operand values of B
 // fragments X ([NQ][NCB], features < K, cells < n) decoded into out[f * n + c]
 hipError_t launch_layer_dbg(int fmt, const LayerArgs &a, hipStream_t s);
 hipError_t launch_frag_decode(int fmt, const uint8_t *X, int NCB, int K, int n, float *out,
                               hipStream_t s);
-hipError_t launch_copy_rows(const float *src, int ld_src, int rows, int n, float *dst,
-                            hipStream_t s);
 
 // Shape and layout of one compiled network configuration.
 struct NetLayout {

@@ -7,16 +7,16 @@
 // matrix product over a chunk of cells, with 256 x 256 output tiles whose
 // operands are staged in LDS, so every weight byte fetched serves 256 cells.
 //
-//   prep_kernel    steps 1-2 (power transform, Z-score) -> layer-1 B fragments
-//   layer_kernel   one layer, Zt = W At (+ b, GELU for hidden layers); the
-//                  output goes straight into the next layer's B fragments
-//   post_kernel    steps 4-7 per cell (one thread per cell, FP64 update)
+//   first_kernel   steps 1-2 (power transform, Z-score) and the first layer
+//   layer_kernel   a hidden layer, Zt = GELU(W At + b)
+//   last_kernel    the output layer and steps 4-7 (FP64 update)
+//
+// each writing the next layer's B fragments.
 //
 // The property networks of the supercritical flame (PRNet, Sec. 2 and the
 // network sizes of Sec. 4: 3-1024-512-256-1 and 3-2048-1024-512-4) run on the
-// same layer kernel between their own input and output maps
-// (prop_prep_kernel: Z-score of the input fields; prop_post_kernel: the
-// output affine map in FP64).
+// same kernels with their own input and output maps (Z-score of the input
+// fields; the output affine map in FP64).
 //
 // Activations live in HBM between layers as "B fragments": for k-step q and
 // cell-block cb (16 cells) a 1 KiB block of 64 lanes x 16 bytes, lane
@@ -95,6 +95,32 @@ using T64 = Tile<2, 2, 2, 2, 4, 2>;    // 64 x 64, four waves of 32 x 32
 using T32 = Tile<2, 1, 2, 2, 4, 2>;    // 32 x 64, two waves of 32 x 32
 using T16 = Tile<2, 1, 1, 1, 8, 2>;    // 32 x 16, one wave
 
+// GELU of the row-blocks rb .. of one k-step (accumulators y), written as the
+// next layer's B fragment of cell-block cb: output row 16 rb + 4 g + r is
+// input feature of k-step rb / RPQ, slot 4 (rb % RPQ) + r.  Row-blocks past R
+// are zero.
+template <class Op>
+__device__ __forceinline__ void put_hidden(uint8_t *Y, int rb, int R, int NCB, int cb, int lane,
+                                           const f4 (&acc)[Op::KS / 16]) {
+  constexpr int RPQ = Op::KS / 16;
+  __attribute__((aligned(16))) uint8_t buf[16];
+#pragma unroll
+  for (int k = 0; k < RPQ; ++k) {
+    f4 y;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      y[r] = gelu(acc[k][r]);
+      // an FP32 value before it is rounded to 16 bits, whatever the
+      // compiler could fuse (v_fma_mix rounds the last product once)
+      asm("" : "+v"(y[r]));
+    }
+    Op::store4(buf + 4 * k * Op::EB, y);
+  }
+  i4 v = *(const i4 *)buf;
+  if (RPQ == 2 && rb + 1 >= R) v[2] = v[3] = 0;
+  *(i4 *)(Y + ((size_t)(rb / RPQ) * NCB + cb) * FB + lane * 16) = v;
+}
+
 }  // namespace
 
 // ------------------------------------------------------------------ layer
@@ -120,7 +146,7 @@ using T16 = Tile<2, 1, 1, 1, 8, 2>;    // 32 x 16, one wave
 // placed between the products: 4096 -> 2048 over 32,768 cells in BF16 takes
 // 450 us (1.22 PFLOP/s) against 518 with a branching loop whose products the
 // compiler had moved behind the next stage's barrier.
-template <class Op, class T, bool ACT, bool DBG = false>
+template <class Op, class T, bool DBG = false>
 __global__ __launch_bounds__(T::NT, 1) void layer_kernel(LayerArgs a) {
   constexpr int WRB = T::WRB, WR = T::WR, WCB = T::WCB, WC = T::WC, ST = T::ST, KG = T::KG;
   constexpr int NW = WR * WC;                         // waves
@@ -281,187 +307,226 @@ __global__ __launch_bounds__(T::NT, 1) void layer_kernel(LayerArgs a) {
           if (row < a.dbg_rows && cell < a.dbg_n) a.dbg_acc[(size_t)row * a.dbg_n + cell] = acc[i][j][r];
         }
   }
-  if constexpr (ACT) {
-    // GELU, then the next layer's B fragments: output row 16 rb + 4 g + r is
-    // input feature of k-step rb / RPQ, slot 4 (rb % RPQ) + r
-    constexpr int RPQ = Op::KS / 16;
-    static_assert(WRB % RPQ == 0, "row-blocks of a k-step in one wave");
+  // GELU, then the next layer's B fragments: output row 16 rb + 4 g + r is
+  // input feature of k-step rb / RPQ, slot 4 (rb % RPQ) + r
+  constexpr int RPQ = Op::KS / 16;
+  static_assert(WRB % RPQ == 0, "row-blocks of a k-step in one wave");
 #pragma unroll
-    for (int i = 0; i < WRB; i += RPQ) {
-      const int rb = rb0 + wr * WRB + i;
-      if (rb >= a.RO) continue;
+  for (int i = 0; i < WRB; i += RPQ) {
+    const int rb = rb0 + wr * WRB + i;
+    if (rb >= a.RO) continue;
 #pragma unroll
-      for (int j = 0; j < WCB; ++j) {
-        const int cb = cb0 + wc * WCB + j;
-        if (cb >= a.NCB) continue;
-        __attribute__((aligned(16))) uint8_t buf[16];
+    for (int j = 0; j < WCB; ++j) {
+      const int cb = cb0 + wc * WCB + j;
+      if (cb >= a.NCB) continue;
+      f4 y[RPQ];
 #pragma unroll
-        for (int k = 0; k < RPQ; ++k) {
-          f4 y;
+      for (int k = 0; k < RPQ; ++k) y[k] = acc[i + k][j];
+      put_hidden<Op>(a.Y, rb, a.R, a.NCB, cb, lane, y);
+    }
+  }
+}
+
+// ------------------------------------------------------------------ first layer
+// The first hidden layer with its input: a wave computes the features of
+// FWCB cell-blocks straight into the B fragments of its lanes (lane: cell cl,
+// group g holds the features frag_feature(KS, q, g, j)) - power transform and
+// Z-score for the chemistry networks, Z-score in FP64 for the property
+// networks (PROP), zero past the inputs and for cells past the chunk - then
+// RPW row-blocks of the layer.  Its 32 inputs are one or two k-steps, so there
+// is nothing to stage: bound by the GELUs and by the writes.  The row parts of
+// a cell group recompute its features, which replaces a launch and a pass
+// over memory: 32,768 cells x 2048 rows in BF16 take 40 us (67 M GELUs take 25
+// us of issue, the 134 MB written 27), with a feature kernel before it and the
+// layer on the tiled kernel 43 us; 1,000 cells 7 against 15 us.
+constexpr int FWCB = 2;
+template <class Op, bool PROP, bool DBG = false>
+__global__ __launch_bounds__(256) void first_kernel(FirstArgs a) {
+  using frag_t = typename Op::frag_t;
+  constexpr int NQ = 32 / Op::KS, NE = 16 / Op::EB, RPQ = Op::KS / 16;
+  const int lane = threadIdx.x & 63, g = lane >> 4, cl = lane & 15;
+  const int id = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int parts = (a.RO + a.RPW - 1) / a.RPW;
+  const int r0 = id % parts * a.RPW, cb0 = id / parts * FWCB;
+  if (cb0 >= a.NCB) return;
+  const int r1 = r0 + a.RPW < a.RO ? r0 + a.RPW : a.RO;
+  const rsrc_t Wr = layer_rsrc(a.W, (uint32_t)a.R * NQ * FB);
+  frag_t x[FWCB][NQ];
+#pragma unroll
+  for (int c = 0; c < FWCB; ++c) {
+    const int cell = 16 * (cb0 + c) + cl;
+    const bool valid = cell < a.nc;
+    const int64_t i = a.n0 + (valid ? cell : 0);
+    double in[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int f = 16 * (j >> 2) + 4 * g + (j & 3);
+      if constexpr (PROP) {
+        in[j] = a.x[(int64_t)(f < a.D ? f : a.D - 1) * a.ld + i];
+      } else {
+        const int s = f - 2 < a.D - 2 ? f - 2 : a.D - 3;
+        in[j] = *(f == 0 ? a.T + i : f == 1 ? a.P + i : a.x + (int64_t)s * a.ld + i);
+      }
+    }
+    typedef decltype(Op::feature(0.0)) elem_t;
+    __attribute__((aligned(16))) elem_t buf[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int f = 16 * (j >> 2) + 4 * g + (j & 3);
+      const bool used = valid && f < a.D;
+      elem_t z;
+      if constexpr (PROP) {
+        z = Op::feature((in[j] - a.dc[PConst::IN_MU + f]) * a.dc[PConst::IN_IS + f]);
+      } else {
+        z = Op::feature(ypow(in[j], a.fc[FConst::LAM]), a.fc[FConst::ZA + f], a.fc[FConst::ZC + f]);
+        if (j < 2) {
+          const elem_t tp = Op::feature((in[j] - a.dc[j == 0 ? DConst::T_MU : DConst::P_MU]) *
+                                        a.dc[j == 0 ? DConst::T_IS : DConst::P_IS]);
+          z = g == 0 ? tp : z;
+        }
+      }
+      z = used ? z : (elem_t)0.0f;
+      if constexpr (DBG)
+        if (used && r0 == 0) a.dbg_in[(size_t)f * a.nc + cell] = (float)z;
+      buf[j] = z;
+    }
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) x[c][q] = *(const frag_t *)(buf + q * NE);
+  }
+  auto load = [&](frag_t (&wf)[RPQ][NQ], f4 (&b)[RPQ], int rb) {
+#pragma unroll
+    for (int k = 0; k < RPQ; ++k) {
+      const int r = rb + k < a.R ? rb + k : a.R - 1;
+#pragma unroll
+      for (int q = 0; q < NQ; ++q)
+        wf[k][q] = __builtin_bit_cast(frag_t, __builtin_amdgcn_raw_buffer_load_b128(
+                                                  Wr, lane * 16, (r * NQ + q) * FB, 0));
+      b[k] = *(const f4 *)(a.bias + 16 * r + 4 * g);
+    }
+  };
+  frag_t wf[RPQ][NQ];
+  f4 bias[RPQ];
+  load(wf, bias, r0);
+  for (int rb = r0; rb < r1; rb += RPQ) {
+    f4 acc[RPQ][FWCB];
+#pragma unroll
+    for (int k = 0; k < RPQ; ++k)
+#pragma unroll
+      for (int c = 0; c < FWCB; ++c) {
+        acc[k][c] = bias[k];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) acc[k][c] = Op::mma(wf[k][q], x[c][q], acc[k][c]);
+      }
+    load(wf, bias, rb + RPQ < r1 ? rb + RPQ : rb);
+#pragma unroll
+    for (int c = 0; c < FWCB; ++c) {
+      const int cb = cb0 + c;
+      if (cb >= a.NCB) continue;
+      if constexpr (DBG)
+#pragma unroll
+        for (int k = 0; k < RPQ; ++k)
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            y[r] = gelu(acc[i + k][j][r]);
-            // an FP32 value before it is rounded to 16 bits, whatever the
-            // compiler could fuse (v_fma_mix rounds the last product once)
-            asm("" : "+v"(y[r]));
+            const int row = 16 * (rb + k) + 4 * g + r, cell = 16 * cb + cl;
+            if (row < a.dbg_rows && cell < a.nc) a.dbg_acc[(size_t)row * a.nc + cell] = acc[k][c][r];
           }
-          Op::store4(buf + 4 * k * Op::EB, y);
-        }
-        i4 v = *(const i4 *)buf;
-        if (RPQ == 2 && rb + 1 >= a.R) v[2] = v[3] = 0;
-        *(i4 *)(a.Y + ((size_t)(rb / RPQ) * a.NCB + cb) * FB + lane * 16) = v;
-      }
+      f4 y[RPQ];
+#pragma unroll
+      for (int k = 0; k < RPQ; ++k) y[k] = acc[k][c];
+      put_hidden<Op>(a.Y, rb, a.R, a.NCB, cb, lane, y);
     }
+  }
+}
+
+// ------------------------------------------------------------------ last layer
+// The output layer (32 rows) and what follows it, a wave per cell-block: the
+// accumulators of its lanes are the rows 16 h + 4 g + r of cell cl, which the
+// chemistry networks' post-processing takes as it does in the fused kernel
+// (post.inc; output rows shifted by two), the property networks' (PROP,
+// unshifted) as y = o sigma + mu in FP64.  Weights and activations go straight
+// to registers, PF k-steps ahead (the weights of a workgroup's four waves
+// come through its L1).  Bound by the state's and the activations' loads and
+// by the FP64 post-processing, whose four lanes per cell run it in a quarter
+// of the time of one: 1,000 cells of the 512-wide layer take 8 us, 32,768
+// 15 us, against 27 and 35 us in a tiled layer and a thread per cell.
+template <class Op, bool PROP, bool DBG = false>
+__global__ __launch_bounds__(256) void last_kernel(LastArgs a) {
+  using frag_t = typename Op::frag_t;
+  constexpr int PF = 8;
+  const int lane = threadIdx.x & 63, g = lane >> 4, cl = lane & 15;
+  const int cb = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (cb >= a.NCB) return;
+  const int cell = 16 * cb + cl;
+  const bool valid = cell < a.nc;
+  const int64_t i = a.n0 + (valid ? cell : 0);
+  double T = 0.0, P = 0.0, Yc[8];
+  if constexpr (!PROP && !DBG) {
+    T = a.T[i];
+    P = a.P[i];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int s = 16 * (j >> 2) + 4 * g + (j & 3) - 2;
+      Yc[j] = a.x[(int64_t)(s < 0 ? 0 : s < a.S ? s : a.S - 1) * a.ld + i];
+    }
+  }
+  const rsrc_t Wr = layer_rsrc(a.W, (uint32_t)2 * a.NQ * FB);
+  const rsrc_t Xr = layer_rsrc(a.X, (uint32_t)a.NQ * a.NCB * FB);
+  frag_t wf[PF][2], xf[PF];
+  auto load = [&](int u, int q) {
+    const int qc = q < a.NQ ? q : a.NQ - 1;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      wf[u][h] = __builtin_bit_cast(frag_t, __builtin_amdgcn_raw_buffer_load_b128(
+                                                Wr, lane * 16, (h * a.NQ + qc) * FB, 0));
+    xf[u] = __builtin_bit_cast(frag_t, __builtin_amdgcn_raw_buffer_load_b128(
+                                           Xr, lane * 16, (int)((uint32_t)(qc * a.NCB + cb) * FB), 0));
+  };
+  f4 o[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) o[h] = *(const f4 *)(a.bias + 16 * h + 4 * g);
+#pragma unroll
+  for (int u = 0; u < PF; ++u) load(u, u);
+  int q = 0;
+  for (; q + PF <= a.NQ; q += PF)
+#pragma unroll
+    for (int u = 0; u < PF; ++u) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) o[h] = Op::mma(wf[u][h], xf[u], o[h]);
+      load(u, q + u + PF);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+  for (int u = 0; u < PF; ++u)
+    if (q + u < a.NQ) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) o[h] = Op::mma(wf[u][h], xf[u], o[h]);
+    }
+  if constexpr (DBG) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int s = 16 * h + 4 * g + r - (PROP ? 0 : 2);
+        if (valid && s >= 0 && s < a.S) a.dbg_acc[(size_t)s * a.nc + cell] = o[h][r];
+      }
+  } else if constexpr (PROP) {
+    if (!valid) return;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int k = 16 * h + 4 * g + r;
+        if (k < a.S)
+          a.Y_out[(int64_t)k * a.ld + i] =
+              __builtin_fma((double)o[h][r], a.dc[PConst::OUT_SD + k], a.dc[PConst::OUT_MU + k]);
+      }
   } else {
-    // output layer: FP32 [row][cell]
-#pragma unroll
-    for (int i = 0; i < WRB; ++i)
-#pragma unroll
-      for (int j = 0; j < WCB; ++j) {
-        const int rb = rb0 + wr * WRB + i, cb = cb0 + wc * WCB + j;
-        if (rb >= a.R || cb >= a.NCB) continue;
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          a.O[(size_t)(16 * rb + 4 * g + r) * a.ldo + 16 * cb + cl] = acc[i][j][r];
-      }
+    constexpr int FRAG = Op::FRAG;
+    const double *const dcl = a.dc;
+    const float *const fcl = a.fc;
+    const float lam = fcl[FConst::LAM], inv_lam = fcl[FConst::INV_LAM];
+#include "post.inc"
   }
-}
-
-// ------------------------------------------------------------------ prep
-// Writes the 32 features z of cell c of the chunk into the layer-1 B
-// fragments X ([32 / KS][NCB] fragments).
-template <class Op>
-__device__ __forceinline__ void store_layer1(const float (&z)[32], uint8_t *X, int NCB, int c) {
-  const int cb = c >> 4, cl = c & 15;
-  constexpr int NE = 16 / Op::EB;                          // slots per lane
-#pragma unroll
-  for (int q = 0; q < 32 / Op::KS; ++q)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      __attribute__((aligned(16))) uint8_t buf[16];
-#pragma unroll
-      for (int j0 = 0; j0 < NE; j0 += 4) {
-        f4 y;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) y[r] = z[frag_feature(Op::KS, q, g, j0 + r)];
-        Op::store4(buf + j0 * Op::EB, y);
-      }
-      *(i4 *)(X + ((size_t)q * NCB + cb) * FB + (g * 16 + cl) * 16) = *(const i4 *)buf;
-    }
-}
-
-// Thread per cell c of the chunk (cells past the chunk give zero features):
-// z_f of steps 1-2 for f < 32, written into the layer-1 B fragments.
-template <class Op>
-__global__ __launch_bounds__(256) void prep_kernel(PrepArgs a) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= 16 * a.NCB) return;
-  const int64_t i = a.n0 + c;
-  const bool valid = c < a.nc;
-  const int64_t ii = valid ? i : 0;
-  const float lam = a.fc[FConst::LAM];
-  float z[32];
-#pragma unroll
-  for (int f = 0; f < 32; ++f) {
-    float v = 0.0f;
-    if (valid) {
-      if (f == 0) {
-        v = (float)((a.T[ii] - a.dc[DConst::T_MU]) * a.dc[DConst::T_IS]);
-      } else if (f == 1) {
-        v = (float)((a.P[ii] - a.dc[DConst::P_MU]) * a.dc[DConst::P_IS]);
-      } else if (f - 2 < a.S) {
-        v = __builtin_fmaf(ypow(a.Y[(int64_t)(f - 2) * a.ld + ii], lam), a.fc[FConst::ZA + f],
-                           a.fc[FConst::ZC + f]);
-      }
-    }
-    z[f] = v;
-  }
-  store_layer1<Op>(z, a.X, a.NCB, c);
-}
-
-// Property network input: thread per cell c of the chunk, z_f = (x_f - mu_f) /
-// sigma_f in FP64 for the n_in input fields (zero for f >= n_in and for cells
-// past the chunk), rounded to FP32 and written into the layer-1 B fragments.
-template <class Op>
-__global__ __launch_bounds__(256) void prop_prep_kernel(PropPrepArgs a) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= 16 * a.NCB) return;
-  const bool valid = c < a.nc;
-  const int64_t i = valid ? a.n0 + c : 0;
-  float z[32];
-#pragma unroll
-  for (int f = 0; f < 32; ++f)
-    z[f] = (valid && f < a.D)
-               ? (float)((a.x[(int64_t)f * a.ld + i] - a.pc[PConst::IN_MU + f]) * a.pc[PConst::IN_IS + f])
-               : 0.0f;
-  store_layer1<Op>(z, a.X, a.NCB, c);
-}
-
-// ------------------------------------------------------------------ post
-// Thread per cell: steps 4-7 from the FP32 network output O[s][cell].  The
-// species loops are unrolled to the 30-species maximum (guarded by S), so
-// the updated fractions stay in registers between the passes.
-__global__ __launch_bounds__(256) void post_kernel(PostArgs a) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= a.nc) return;
-  const int64_t i = a.n0 + c;
-  const float lam = a.fc[FConst::LAM], inv_lam = a.fc[FConst::INV_LAM];
-  const double T = a.T[i], P = a.P[i], t_ref = a.dc[DConst::T_REF];
-  bool bad = !__builtin_isfinite(T) || !__builtin_isfinite(P);
-  constexpr int SMAX = 30;
-  double y[SMAX], yh[SMAX];
-  double ssum = 0.0, h0 = 0.0, ry = 0.0;
-#pragma unroll
-  for (int s = 0; s < SMAX; ++s) {
-    y[s] = 0.0;
-    yh[s] = 0.0;
-    if (s >= a.S) continue;
-    const int rho = s + 2;
-    y[s] = a.Y[(int64_t)s * a.ld + i];
-    bad |= !__builtin_isfinite(y[s]);
-    const float o = a.O[(size_t)s * a.ldo + c];
-    const float wv = __builtin_fmaf(o, a.fc[FConst::PA + rho], a.fc[FConst::PB + rho]);
-    const double v = y[s] + inv_change(y[s], wv, lam, inv_lam);
-    // a NaN network output or a non-finite result flags the cell (the inverse
-    // transform takes a NaN base like a negative one; the clamp turns NaN into 0)
-    bad |= __builtin_isnan(wv) || !__builtin_isfinite(v);
-    yh[s] = v > 0.0 ? v : 0.0;
-    ssum += yh[s];
-    h0 += y[s] * (a.dc[DConst::HF + rho] + a.dc[DConst::CP + rho] * (T - t_ref));
-    ry += y[s] * a.dc[DConst::WINV + rho];
-  }
-  const double rsum = 1.0 / ssum;
-  double hn = 0.0, cn = 0.0;
-  bool nonfin = false;
-#pragma unroll
-  for (int s = 0; s < SMAX; ++s) {
-    if (s >= a.S) continue;
-    const double yn = yh[s] * rsum;
-    nonfin |= !__builtin_isfinite(yn);
-    hn += yn * a.dc[DConst::HF + s + 2];
-    cn += yn * a.dc[DConst::CP + s + 2];
-  }
-  const double Tn = a.thermo ? t_ref + (h0 - hn) / cn : T;
-  const bool okc = !bad && !nonfin && ssum > 0.0 && __builtin_isfinite(ssum) && __builtin_isfinite(Tn);
-  const double rho_dt = a.omega && okc ? P / (kRGas * T * ry) * a.inv_dt : 0.0;
-#pragma unroll
-  for (int s = 0; s < SMAX; ++s) {
-    if (s >= a.S) continue;
-    const double yn = okc ? yh[s] * rsum : y[s];
-    a.Y_out[(int64_t)s * a.ld + i] = yn;
-    if (a.omega) a.omega[(int64_t)s * a.ld + i] = okc ? rho_dt * (yn - y[s]) : 0.0;
-  }
-  if (a.T_out) a.T_out[i] = okc ? Tn : T;
-  if (!okc && a.n_bad) atomicAdd(a.n_bad, 1u);
-}
-
-// Property network output: y_k = o_k sigma_k + mu_k in FP64, thread per
-// (output k, cell c); FP32 network output O[k][ldo] of the chunk.
-__global__ __launch_bounds__(256) void prop_post_kernel(PropPostArgs a) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x, k = blockIdx.y;
-  if (c >= a.nc) return;
-  const double o = a.O[(size_t)k * a.ldo + c];
-  a.y[(int64_t)k * a.ld + a.n0 + c] = __builtin_fma(o, a.pc[PConst::OUT_SD + k], a.pc[PConst::OUT_MU + k]);
 }
 
 // ------------------------------------------------------------------ debug
@@ -477,18 +542,7 @@ __global__ __launch_bounds__(256) void frag_decode_kernel(const uint8_t *X, int 
   const int q = f / Op::KS, rr = f % Op::KS;
   const int j = 4 * (rr / 16) + rr % 4, g = (rr % 16) / 4;
   const uint8_t *p = X + ((size_t)(q * NCB + c / 16) * 64 + g * 16 + c % 16) * 16 + j * Op::EB;
-  float v;
-  if constexpr (__is_same(Op, OpF32)) v = *(const float *)p;
-  else if constexpr (__is_same(Op, OpBF16)) v = (float)*(const __bf16 *)p;
-  else v = (float)*(const _Float16 *)p;
-  out[t] = v;
-}
-
-__global__ __launch_bounds__(256) void copy_rows_kernel(const float *src, int ld_src, int rows, int n,
-                                                        float *dst) {
-  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (t >= (int64_t)rows * n) return;
-  dst[t] = src[(t / n) * (int64_t)ld_src + t % n];
+  out[t] = (float)*(const decltype(Op::feature(0.0)) *)p;
 }
 
 // ------------------------------------------------------------------ launchers
@@ -499,9 +553,9 @@ hipError_t set_lds(K kern, int bytes) {
   return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
-template <class Op, class T, bool ACT, bool DBG = false>
+template <class Op, class T, bool DBG = false>
 hipError_t launch_tile(const LayerArgs &a, hipStream_t s) {
-  auto k = layer_kernel<Op, T, ACT, DBG>;
+  auto k = layer_kernel<Op, T, DBG>;
   const int grid = ((a.R + T::TRB - 1) / T::TRB) * ((a.NCB + T::TCB - 1) / T::TCB);
   hipLaunchKernelGGL(k, dim3(grid), dim3(T::NT), T::LDS, s, a);
   return hipGetLastError();
@@ -538,14 +592,13 @@ int pick_tile(const TileCost (&cost)[5], const LayerArgs &a) {
 }
 
 template <class Op>
-hipError_t launch_layer_op(const LayerArgs &a, bool hidden, hipStream_t s) {
-  if (!hidden) return launch_tile<Op, T32, false>(a, s);
+hipError_t launch_layer_op(const LayerArgs &a, hipStream_t s) {
   switch (pick_tile(Op::EB == 4 ? kCost32 : kCost16, a)) {
-    case 0: return launch_tile<Op, T256, true>(a, s);
-    case 1: return launch_tile<Op, T128, true>(a, s);
-    case 2: return launch_tile<Op, T64, true>(a, s);
-    case 3: return launch_tile<Op, T32, true>(a, s);
-    default: return launch_tile<Op, T16, true>(a, s);
+    case 0: return launch_tile<Op, T256>(a, s);
+    case 1: return launch_tile<Op, T128>(a, s);
+    case 2: return launch_tile<Op, T64>(a, s);
+    case 3: return launch_tile<Op, T32>(a, s);
+    default: return launch_tile<Op, T16>(a, s);
   }
 }
 
@@ -553,11 +606,11 @@ hipError_t launch_layer_op(const LayerArgs &a, bool hidden, hipStream_t s) {
 template <class Op>
 hipError_t launch_layer_dbg_op(const LayerArgs &a, hipStream_t s) {
   switch (pick_tile(Op::EB == 4 ? kCost32 : kCost16, a)) {
-    case 0: return launch_tile<Op, T256, true, true>(a, s);
-    case 1: return launch_tile<Op, T128, true, true>(a, s);
-    case 2: return launch_tile<Op, T64, true, true>(a, s);
-    case 3: return launch_tile<Op, T32, true, true>(a, s);
-    default: return launch_tile<Op, T16, true, true>(a, s);
+    case 0: return launch_tile<Op, T256, true>(a, s);
+    case 1: return launch_tile<Op, T128, true>(a, s);
+    case 2: return launch_tile<Op, T64, true>(a, s);
+    case 3: return launch_tile<Op, T32, true>(a, s);
+    default: return launch_tile<Op, T16, true>(a, s);
   }
 }
 
@@ -586,21 +639,13 @@ hipError_t launch_frag_decode(int fmt, const uint8_t *X, int NCB, int K, int n, 
   return hipGetLastError();
 }
 
-hipError_t launch_copy_rows(const float *src, int ld_src, int rows, int n, float *dst, hipStream_t s) {
-  const int64_t total = (int64_t)rows * n;
-  if (total <= 0) return hipSuccess;
-  hipLaunchKernelGGL(copy_rows_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, src,
-                     ld_src, rows, n, dst);
-  return hipGetLastError();
-}
-
 // The layer kernels use more than the default 64 KiB of LDS.
-template <class Op, class T, bool ACT, bool DBG = false> static hipError_t prepare_tile() {
-  return set_lds(layer_kernel<Op, T, ACT, DBG>, T::LDS);
+template <class Op, class T, bool DBG = false> static hipError_t prepare_tile() {
+  return set_lds(layer_kernel<Op, T, DBG>, T::LDS);
 }
 template <class Op> static hipError_t prepare_op() {
-  hipError_t e = prepare_tile<Op, T256, true>();   // (the other tiles: at most 64 KiB)
-  if (e == hipSuccess) e = prepare_tile<Op, T256, true, true>();
+  hipError_t e = prepare_tile<Op, T256>();   // (the other tiles: at most 64 KiB)
+  if (e == hipSuccess) e = prepare_tile<Op, T256, true>();
   static_assert(T128::LDS <= 65536 && T64::LDS <= 65536 && T32::LDS <= 65536 && T16::LDS <= 65536, "LDS");
   return e;
 }
@@ -611,47 +656,54 @@ hipError_t layered_prepare() {
   return e;
 }
 
-hipError_t launch_layer(int fmt, const LayerArgs &a, bool hidden, hipStream_t s) {
+hipError_t launch_layer(int fmt, const LayerArgs &a, hipStream_t s) {
   switch (fmt) {
-    case 0: return launch_layer_op<OpF32>(a, hidden, s);
-    case 1: return launch_layer_op<OpBF16>(a, hidden, s);
-    case 2: return launch_layer_op<OpF16>(a, hidden, s);
+    case 0: return launch_layer_op<OpF32>(a, s);
+    case 1: return launch_layer_op<OpBF16>(a, s);
+    case 2: return launch_layer_op<OpF16>(a, s);
     default: return hipErrorInvalidValue;
   }
 }
 
-hipError_t launch_prep(int fmt, const PrepArgs &a, hipStream_t s) {
-  const int blocks = (16 * a.NCB + 255) / 256;
+namespace {
+
+template <class Op> hipError_t launch_first_op(const FirstArgs &a0, bool prop, bool dbg, hipStream_t s) {
+  FirstArgs a = a0;
+  // row-blocks per wave: few enough that about 16 waves per CU have work, at
+  // most 32 (features recomputed once per 32 row-blocks cost nothing any more)
+  const int64_t groups = (a.NCB + FWCB - 1) / FWCB;
+  int64_t rpw = groups * a.RO / (16 * (int64_t)a.n_cu) / 2 * 2;
+  a.RPW = (int)(rpw < 4 ? 4 : rpw > 32 ? 32 : rpw);
+  const int64_t waves = groups * ((a.RO + a.RPW - 1) / a.RPW);
+  const dim3 grid((unsigned)((waves + 3) / 4));
+  auto k = prop ? first_kernel<Op, true> : dbg ? first_kernel<Op, false, true> : first_kernel<Op, false>;
+  hipLaunchKernelGGL(k, grid, dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+template <class Op> hipError_t launch_last_op(const LastArgs &a, bool prop, bool dbg, hipStream_t s) {
+  auto k = prop ? last_kernel<Op, true> : dbg ? last_kernel<Op, false, true> : last_kernel<Op, false>;
+  hipLaunchKernelGGL(k, dim3((a.NCB + 3) / 4), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_first(int fmt, const FirstArgs &a, bool prop, bool dbg, hipStream_t s) {
   switch (fmt) {
-    case 0: hipLaunchKernelGGL(prep_kernel<OpF32>, dim3(blocks), dim3(256), 0, s, a); break;
-    case 1: hipLaunchKernelGGL(prep_kernel<OpBF16>, dim3(blocks), dim3(256), 0, s, a); break;
-    case 2: hipLaunchKernelGGL(prep_kernel<OpF16>, dim3(blocks), dim3(256), 0, s, a); break;
+    case 0: return launch_first_op<OpF32>(a, prop, dbg, s);
+    case 1: return launch_first_op<OpBF16>(a, prop, dbg, s);
+    case 2: return launch_first_op<OpF16>(a, prop, dbg, s);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
-hipError_t launch_prop_prep(int fmt, const PropPrepArgs &a, hipStream_t s) {
-  const int blocks = (16 * a.NCB + 255) / 256;
+hipError_t launch_last(int fmt, const LastArgs &a, bool prop, bool dbg, hipStream_t s) {
   switch (fmt) {
-    case 0: hipLaunchKernelGGL(prop_prep_kernel<OpF32>, dim3(blocks), dim3(256), 0, s, a); break;
-    case 1: hipLaunchKernelGGL(prop_prep_kernel<OpBF16>, dim3(blocks), dim3(256), 0, s, a); break;
-    case 2: hipLaunchKernelGGL(prop_prep_kernel<OpF16>, dim3(blocks), dim3(256), 0, s, a); break;
+    case 0: return launch_last_op<OpF32>(a, prop, dbg, s);
+    case 1: return launch_last_op<OpBF16>(a, prop, dbg, s);
+    case 2: return launch_last_op<OpF16>(a, prop, dbg, s);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
-}
-
-hipError_t launch_prop_post(const PropPostArgs &a, hipStream_t s) {
-  if (a.nc <= 0 || a.K <= 0) return hipSuccess;
-  hipLaunchKernelGGL(prop_post_kernel, dim3((a.nc + 255) / 256, a.K), dim3(256), 0, s, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_post(const PostArgs &a, hipStream_t s) {
-  if (a.nc <= 0) return hipSuccess;
-  hipLaunchKernelGGL(post_kernel, dim3((a.nc + 255) / 256), dim3(256), 0, s, a);
-  return hipGetLastError();
 }
 
 }  // namespace chemdnn

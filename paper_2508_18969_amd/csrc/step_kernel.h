@@ -172,13 +172,6 @@ __device__ __forceinline__ unsigned opaque_u(unsigned v) {
   asm volatile("" : "+s"(v));
   return v;
 }
-// The same for a per-lane value: LDS addresses built on it keep their
-// constant parts in the instruction's offset field.
-__device__ __forceinline__ int opaque_v(int v) {
-  asm volatile("" : "+v"(v));
-  return v;
-}
-
 // PROP: property mode - the input features are the Z-scored fields x[f]
 // (f < D) and the output rows 2 .. K+1 are scaled to y[k] = o sigma_k + mu_k;
 // dc is then a PConst block.
@@ -921,86 +914,7 @@ __global__ __launch_bounds__(C::NW * 64, 1) void chem_step_kernel(StepArgs a) {
         Yc[j] = y2[0];
         Yc[j + 1] = y2[1];
       }
-      bool bad = !__builtin_isfinite(T) || !__builtin_isfinite(P);
-      double Y[8], Yh[8];
-      double ssum = 0.0, h0 = 0.0;
-      const double t_ref = dcl[DConst::T_REF];
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          // every row is evaluated (no branches); rows that are not species
-          // take y = 0 and are zeroed at the end
-          const int rho = 16 * h + 4 * g + r, s = rho - 2, j = 4 * h + r;
-          const bool sp = s >= 0 && s < a.S;
-          {
-            const double y = sp ? Yc[j] : 0.0;
-            Y[j] = y;
-            bad |= !__builtin_isfinite(y);
-            const float wv = __builtin_fmaf(o[h][r], fcl[FConst::PA + rho], fcl[FConst::PB + rho]);
-            double yh = y + inv_change(y, wv, lam, inv_lam);
-            // a NaN network output or a non-finite result flags the cell (the
-            // inverse transform takes a NaN base like a negative one, and the
-            // clamp below would turn a NaN into 0)
-            bad |= sp && (__builtin_isnan(wv) || !__builtin_isfinite(yh));
-            yh = sp && yh > 0.0 ? yh : 0.0;
-            Yh[j] = yh;
-            ssum += yh;
-            // (the tables are zero past the species rows and without thermo data)
-            h0 += y * (dcl[DConst::HF + rho] + dcl[DConst::CP + rho] * (T - t_ref));
-          }
-        }
-      // the cell's four lanes: l, l^16, l^32, l^48
-      ssum = quad_sum(ssum);
-      double Yn[8];
-      double hn = 0.0, cn = 0.0;
-      const double rsum = 1.0 / ssum;
-      uint32_t nonfin = 0u;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        Yn[j] = Yh[j] * rsum;
-        nonfin |= __builtin_isfinite(Yn[j]) ? 0u : 1u;
-        const int rho = 16 * (j >> 2) + 4 * g + (j & 3);
-        hn += Yn[j] * dcl[DConst::HF + rho];
-        cn += Yn[j] * dcl[DConst::CP + rho];
-      }
-      double Tn = T;
-      if (a.thermo) {
-        h0 = quad_sum(h0);
-        hn = quad_sum(hn);
-        cn = quad_sum(cn);
-        Tn = t_ref + (h0 - hn) / cn;
-      }
-      const uint32_t badq = quad_or((bad ? 1u : 0u) | nonfin);
-      const bool okc = !badq && ssum > 0.0 && __builtin_isfinite(ssum) && __builtin_isfinite(Tn);
-      // species source terms: ideal-gas density of the state before the step
-      double rho_dt = 0.0;
-      if (a.omega) {
-        double ry = 0.0;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) ry += Y[j] * dcl[DConst::WINV + 16 * (j >> 2) + 4 * g + (j & 3)];
-        ry = quad_sum(ry);
-        rho_dt = okc ? P / (kRGas * T * ry) * a.inv_dt : 0.0;
-      }
-      if (valid) {
-        // (FP8: row offsets from an opaque copy of the lane group, recomputed
-        // here instead of being kept, or spilled, across the tile loop)
-        const int go = FRAG == 32 ? opaque_v(g) : g;
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int s = 16 * h + 4 * go + r - 2, j = 4 * h + r;
-            if (s >= 0 && s < a.S) {
-              __builtin_nontemporal_store(okc ? Yn[j] : Y[j], &a.Y_out[(int64_t)s * a.ld + i]);
-              if (a.omega) __builtin_nontemporal_store(okc ? rho_dt * (Yn[j] - Y[j]) : 0.0, &a.omega[(int64_t)s * a.ld + i]);
-            }
-          }
-        if (g == 0) {
-          if (a.T_out) __builtin_nontemporal_store(okc ? Tn : T, &a.T_out[i]);
-          if (!okc && a.n_bad) atomicAdd(a.n_bad, 1u);
-        }
-      }
+#include "post.inc"
     }
   }
 
