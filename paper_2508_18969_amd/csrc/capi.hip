@@ -213,6 +213,7 @@ int32_t plan(const chem_dnn_desc *d, NetLayout *lay, WsPlan *p) {
       p->act[b] = off;
       off = align_up(off + (size_t)kmax * kChunk * eb);
     }
+    off = align_up(off + (size_t)32 * kChunk * sizeof(float));   // reserved (the documented minimum)
   }
   p->train = off;
   off += fused ? train_scratch_bytes(d->widths, d->max_batch, d->recompute_chunk) : 0;
@@ -414,6 +415,7 @@ int32_t prop_plan(const chem_prop_desc *d, PropPlan *p) {
     p->act[b] = off;
     off = align_up(off + (size_t)kmax * p->chunk * eb);
   }
+  off = align_up(off + (size_t)32 * p->chunk * sizeof(float));   // reserved (the documented minimum)
   p->total = off;
   return CHEM_DNN_OK;
 }
