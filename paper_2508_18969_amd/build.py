@@ -17,7 +17,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libchemdnn.so")
 SOURCES = ["step_fp32.hip", "step_bf16.hip", "step_fp16.hip", "step_fp8.hip", "step.hip",
-           "layered.hip", "train.hip", "capi.hip"]
+           "layered.hip", "train.hip", "train_tile.hip", "capi.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [

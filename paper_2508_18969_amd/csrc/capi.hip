@@ -32,6 +32,9 @@ struct chem_dnn {
   float *bias[8];
   void *wpack[8];
   TrainScratch tr;
+  int tiled;           // the small network's training path (train_tile.hip)
+  int tile_ready;      // its kernels' attributes are set
+  TileScratch tt;
   int64_t max_batch;
   int64_t recompute_chunk;
   int thermo;
@@ -216,7 +219,9 @@ int32_t plan(const chem_dnn_desc *d, NetLayout *lay, WsPlan *p) {
     off = align_up(off + (size_t)32 * kChunk * sizeof(float));   // reserved (the documented minimum)
   }
   p->train = off;
-  off += fused ? train_scratch_bytes(d->widths, d->max_batch, d->recompute_chunk) : 0;
+  if (fused)
+    off += tile_shape(d->widths) ? tile_scratch_bytes(d->widths, d->max_batch, d->recompute_chunk)
+                                 : train_scratch_bytes(d->widths, d->max_batch, d->recompute_chunk);
   p->total = align_up(off);
   return CHEM_DNN_OK;
 }
@@ -452,6 +457,27 @@ hipError_t (*step_launch(const chem_dnn *h))(const StepArgs &, int, hipStream_t)
                                                  : h->lay.step;
 }
 
+// A handle made without training (max_batch = 0) sets the training kernels'
+// attributes with its first training call.
+int32_t tile_ready(chem_dnn *h) {
+  if (!h->tile_ready) {
+    if (tile_prepare_all() != hipSuccess) return CHEM_DNN_EHIP;
+    h->tile_ready = 1;
+  }
+  return CHEM_DNN_OK;
+}
+
+// A training step of the small network, Adam's bias corrections in FP64.
+int32_t tiled_step(chem_dnn *h, int64_t B, int64_t ld, const double *T, const double *P,
+                   const double *Y, const float *target, float *params, float *grads, float *adam_m,
+                   float *adam_v, int64_t step, float lr, float *loss, const TileScratch *t,
+                   hipStream_t s) {
+  if (int32_t st = tile_ready(h)) return st;
+  const double c1 = 1.0 / (1.0 - pow(0.9, (double)step)), c2 = 1.0 / (1.0 - pow(0.999, (double)step));
+  return hip_status(tile_train_step(h->widths, B, ld, T, P, Y, target, params, grads, adam_m, adam_v,
+                                    lr, (float)c1, (float)c2, loss, h->fc, h->dc, t, h->n_cu, s));
+}
+
 int grid_for(const chem_dnn *h, int64_t ntiles) {
   int64_t g = ntiles < h->n_cu ? ntiles : h->n_cu;
   return (int)(g < 1 ? 1 : g);
@@ -506,7 +532,9 @@ int32_t chem_dnn_init(const chem_dnn_desc *d, const float *params, void *workspa
   // the static scratch of the allocation-free training step (fused shapes)
   if (!layered && (st = scratch_init(dev)) != CHEM_DNN_OK) return st;
   if ((layered ? layered_prepare() : lay.prepare()) != hipSuccess) return CHEM_DNN_EHIP;
-  if (d->max_batch > 0 && train_prepare() != hipSuccess) return CHEM_DNN_EHIP;
+  const bool tiled = !layered && tile_shape(d->widths);
+  if (d->max_batch > 0 && (tiled ? tile_prepare_all() : train_prepare()) != hipSuccess)
+    return CHEM_DNN_EHIP;
 
   chem_dnn *h = new (std::nothrow) chem_dnn();
   if (!h) return CHEM_DNN_EHIP;
@@ -544,7 +572,10 @@ int32_t chem_dnn_init(const chem_dnn_desc *d, const float *params, void *workspa
   }
   h->max_batch = d->max_batch;
   h->recompute_chunk = d->recompute_chunk;
-  train_scratch_layout(&h->tr, h->ws + p.train, d->widths, d->max_batch, d->recompute_chunk);
+  h->tiled = tiled ? 1 : 0;
+  h->tile_ready = d->max_batch > 0;
+  if (tiled) tile_scratch_layout(&h->tt, h->ws + p.train, d->widths, d->max_batch, d->recompute_chunk);
+  else train_scratch_layout(&h->tr, h->ws + p.train, d->widths, d->max_batch, d->recompute_chunk);
   h->thermo = d->thermo_hf ? 1 : 0;
   h->molar = d->molar_mass ? 1 : 0;
   h->gelu_form = d->gelu_form;
@@ -686,6 +717,11 @@ int32_t chem_dnn_mlp_forward(chem_dnn *h, int64_t B, int64_t ld, const float *x,
   if (B == 0) return CHEM_DNN_OK;
   if (!x || !params || !out) return CHEM_DNN_EINVAL;
   if (!saved && B > h->max_batch) return CHEM_DNN_EINVAL;
+  if (h->tiled) {
+    if (int32_t st = tile_ready(h)) return st;
+    return hip_status(tile_mlp_forward(h->widths, B, ld, x, params, out, saved, &h->tt, h->n_cu,
+                                       (hipStream_t)stream));
+  }
   return hip_status(train_mlp_forward(h->widths, B, ld, x, params, out, saved, &h->tr,
                                       (hipStream_t)stream));
 }
@@ -698,6 +734,9 @@ int32_t chem_dnn_mlp_backward(chem_dnn *h, int64_t B, int64_t ld, const float *x
   if (!params || !grad_params) return CHEM_DNN_EINVAL;
   if (B > 0 && (!x || !grad_out)) return CHEM_DNN_EINVAL;
   if (B > h->max_batch) return CHEM_DNN_EINVAL;
+  if (h->tiled)
+    return hip_status(tile_mlp_backward(h->widths, B, ld, x, params, saved, grad_out, grad_params,
+                                        grad_x, &h->tt, h->n_cu, (hipStream_t)stream));
   return hip_status(train_mlp_backward(h->widths, B, ld, x, params, saved, grad_out,
                                        grad_params, grad_x, &h->tr, (hipStream_t)stream));
 }
@@ -711,6 +750,9 @@ int32_t chem_dnn_train_step(chem_dnn *h, int64_t B, int64_t ld, const double *T,
   if (!T || !P || !Y || !target || !params || !grads || !adam_m || !adam_v || !loss)
     return CHEM_DNN_EINVAL;
   if (!(lr > 0.0f)) return CHEM_DNN_EINVAL;
+  if (h->tiled)
+    return tiled_step(h, B, ld, T, P, Y, target, params, grads, adam_m, adam_v, step, lr, loss,
+                      &h->tt, (hipStream_t)stream);
   return hip_status(train_step(h->widths, B, ld, T, P, Y, target, params, grads, adam_m, adam_v,
                                step, lr, recompute != 0, loss, h->fc, h->dc, &h->tr,
                                (hipStream_t)stream));
@@ -732,6 +774,14 @@ int32_t chem_dnn_train_step_noalloc(chem_dnn *h, int64_t B, int64_t ld, const do
   const int64_t cap = (B + 15) / 16 * 16;
   if (train_scratch_bytes(h->widths, cap, h->recompute_chunk) > CHEM_DNN_NOALLOC_SCRATCH_BYTES)
     return CHEM_DNN_ETOOLARGE;
+  if (h->tiled) {
+    if (tile_scratch_bytes(h->widths, cap, h->recompute_chunk) > CHEM_DNN_NOALLOC_SCRATCH_BYTES)
+      return CHEM_DNN_ETOOLARGE;
+    TileScratch tt;
+    tile_scratch_layout(&tt, base, h->widths, cap, h->recompute_chunk);
+    return tiled_step(h, B, ld, T, P, Y, target, params, grads, adam_m, adam_v, step, lr, loss, &tt,
+                      (hipStream_t)stream);
+  }
   TrainScratch t;
   train_scratch_layout(&t, base, h->widths, cap, h->recompute_chunk);
   return hip_status(train_step(h->widths, B, ld, T, P, Y, target, params, grads, adam_m, adam_v,

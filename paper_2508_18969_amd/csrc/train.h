@@ -44,4 +44,32 @@ hipError_t train_step(const int *widths, int64_t B, int64_t ld, const double *T,
                       float *loss, const float *fc, const double *dc, TrainScratch *t,
                       hipStream_t s);
 
+// The small network's path by tiles of samples (train_tile.hip).
+struct TileScratch {
+  int64_t cap;            // max batch
+  int64_t chunk;          // samples per chunk
+  uint8_t *pack;          // split weight fragments (also without training)
+  float *blk;             // per tile of 32 samples: input, activations and gradients
+  float *part;            // parameter-gradient partials, one copy per split
+  float *lpart;           // loss partial sum per tile
+  double *closs;          // loss sum of each chunk
+};
+bool tile_shape(const int *widths);
+size_t tile_scratch_bytes(const int *widths, int64_t max_batch, int64_t chunk);
+void tile_scratch_layout(TileScratch *t, uint8_t *base, const int *widths, int64_t max_batch,
+                         int64_t chunk);
+hipError_t tile_prepare_all();
+hipError_t tile_mlp_forward(const int *widths, int64_t B, int64_t ld, const float *x,
+                            const float *params, float *out, float *saved, const TileScratch *t,
+                            int n_cu, hipStream_t s);
+hipError_t tile_mlp_backward(const int *widths, int64_t B, int64_t ld, const float *x,
+                             const float *params, const float *saved, const float *grad_out,
+                             float *grad_params, float *grad_x, const TileScratch *t, int n_cu,
+                             hipStream_t s);
+hipError_t tile_train_step(const int *widths, int64_t B, int64_t ld, const double *T, const double *P,
+                           const double *Y, const float *target, float *params, float *grads,
+                           float *adam_m, float *adam_v, float lr, float c1, float c2, float *loss,
+                           const float *fc, const double *dc, const TileScratch *t, int n_cu,
+                           hipStream_t s);
+
 }  // namespace chemdnn

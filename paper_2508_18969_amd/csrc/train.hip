@@ -1,4 +1,5 @@
-// Training kernels (FP32): a strided MFMA GEMM with fused epilogues,
+// Training kernels (FP32) of the networks that train_tile.hip does not cover
+// (31-1600-800-400-29): a strided MFMA GEMM with fused epilogues,
 // deterministic split-K weight gradients, MSE loss and Adam.
 //
 // Forward  z_l = W_l a_(l-1) + b_l, a_l = GELU(z_l) (GELU is applied inside
