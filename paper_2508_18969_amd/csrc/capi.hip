@@ -20,6 +20,7 @@ struct chem_dnn {
   NetLayout lay;
   // layer-by-layer path (networks the fused kernel does not cover)
   int layered;
+  int64_t chain;       // fused networks: most cells of a batch's rest that go layer by layer
   int lR[8], lNQ[8];   // per layer: output row-blocks, input k-steps
   uint8_t *act[2];     // activation fragment buffers of one chunk
   int dev, n_cu;
@@ -55,7 +56,7 @@ struct chem_prop {
   NetLayout lay;         // fused: compiled layout
   int n_cu;
   int lR[8], lNQ[8];     // layer by layer: output row-blocks, input k-steps
-  int64_t chunk;         // cells per chunk
+  int64_t chunk;         // cells per chunk (fused: most cells that go layer by layer)
   uint8_t *ws;
   size_t ws_bytes;
   double *pc;            // PConst block
@@ -146,6 +147,37 @@ bool layered_shape_ok(const chem_dnn_desc *d) {
 int ks_of(int prec) { return prec == CHEM_DNN_FP32 ? 16 : 32; }
 int eb_of(int prec) { return prec == CHEM_DNN_FP32 ? 4 : 2; }
 
+// Fused networks: the most cells of a batch's rest (what whole rounds of the
+// fused kernel's tiles leave) that run layer by layer instead.  A fused tile
+// streams all the weights through one CU, whatever its cells; the layer
+// kernels split them over the chip, so small rests of a large network gain:
+// 31-1600-800-400-29 takes, at 16 / 1,000 / 4,096 / 6,000 cells, 46 / 47 / 49
+// / 50 us fused and 18 / 28 / 46 / 64 layer by layer in BF16, 211 / 214 / 215
+// / 215 and 39 / 64 / 149 / 198 in FP32; 3-1024-512-256-1 in FP32 90 / 91 / 92
+// / 93 and 27 / 41 / 63 / 88.  Networks below 1 MiB are not worth four
+// launches (19-400-200-100-17 in BF16 at 1,000 cells: 16.6 against 17.1).  A
+// property network's buffers keep to the workspace slack that its description
+// allows in 16 bits (256 cells: 23.6 us fused, 15.5 layer by layer).
+// FP8 and the tabulated GELU have no layer kernels.
+// Behind whole rounds the layer kernels have to wait for the last fused tile,
+// while a fused rest starts on the CUs that are done: there the limit is
+// lower (2/3 in FP32, half in 16 bits): of the first network, 16,384 + 2,048
+// cells in FP16 take 101 us fused and 95 in two parts, 16,384 + 3,627 take 102
+// and 103; 8,192 + 4,008 cells in FP32 419 and 366.
+int64_t chain_cells(int prec, const NetLayout &lay, int gelu_form, bool prop) {
+  if (prec == CHEM_DNN_FP8E4M3 || gelu_form != CHEM_DNN_GELU_TANH) return 0;
+  size_t weights = 0;
+  for (int l = 0; l < 4; ++l) weights += (size_t)lay.R[l] * 16 * lay.NQ[l] * lay.KS * lay.EB;
+  if (weights < (size_t)1 << 20) return 0;
+  return prec == CHEM_DNN_FP32 ? 6144 : prop ? 256 : 4096;
+}
+// Activation buffer b of the layer-by-layer kernels for `cells` cells of a
+// fused network: its layers' outputs alternate between the two.
+size_t chain_act_bytes(const NetLayout &lay, int b, int64_t cells) {
+  const int nq = b == 0 ? (lay.NQ[1] > lay.NQ[3] ? lay.NQ[1] : lay.NQ[3]) : lay.NQ[2];
+  return (size_t)nq * lay.KS * lay.EB * (size_t)cells;
+}
+
 int32_t check_desc(const chem_dnn_desc *d) {
   if (!d) return CHEM_DNN_EINVAL;
   const int S = d->n_species, L = d->n_layers;
@@ -199,7 +231,10 @@ int32_t plan(const chem_dnn_desc *d, NetLayout *lay, WsPlan *p) {
       p->w[l] = off;
       off = align_up(off + (size_t)lay->R[l] * 16 * lay->NQ[l] * lay->KS * lay->EB);
     }
-    p->act[0] = p->act[1] = 0;
+    for (int b = 0; b < 2; ++b) {
+      p->act[b] = off;
+      off = align_up(off + chain_act_bytes(*lay, b, chain_cells(d->precision, *lay, d->gelu_form, false)));
+    }
   } else {
     const int ks = ks_of(d->precision), eb = eb_of(d->precision);
     int kmax = 32;
@@ -306,37 +341,90 @@ StepArgs step_args(chem_dnn *h, int64_t n, int64_t ld, const double *T, const do
   return a;
 }
 
-// The layer-by-layer path over chunks of kChunk cells: the first layer with
-// the input transform, one launch per further hidden layer, the output layer
-// with the post-processing.
+// The layers of a network on the layer-by-layer kernels: packed weights,
+// biases, row-blocks and input k-steps per layer, activation buffers.
+struct LayerNet {
+  int fmt, L, n_cu;      // fmt: 0 FP32, 1 BF16, 2 FP16 operands
+  const int *R, *NQ;
+  void *const *w;
+  float *const *b;
+  uint8_t *const *act;
+};
+
+// One chunk: the first layer with the input transform, one launch per further
+// hidden layer, the output layer with the post-processing.  `fa` and `ea`
+// hold the fields; the rest is filled in here.
+hipError_t run_layers(const LayerNet &n, FirstArgs fa, LastArgs ea, int nc, bool prop, bool fused,
+                      hipStream_t s) {
+  const int ncb = (nc + 15) / 16, L = n.L, ks = ks_of(n.fmt);
+  fa.nc = nc;
+  fa.NCB = ncb;
+  fa.W = (const uint8_t *)n.w[0];
+  fa.bias = n.b[0];
+  fa.Y = n.act[0];
+  fa.R = n.R[0];
+  fa.RO = n.NQ[1] * ks / 16;
+  fa.n_cu = n.n_cu;
+  hipError_t e = launch_first(n.fmt, fa, prop, fused, false, s);
+  int cur = 0;
+  for (int l = 1; l < L - 1 && e == hipSuccess; ++l) {
+    LayerArgs la{(const uint8_t *)n.w[l], n.b[l], n.act[cur], n.act[cur ^ 1], n.R[l], n.NQ[l], ncb,
+                 n.NQ[l + 1] * ks / 16, n.n_cu, nullptr, 0, 0};
+    e = launch_layer(n.fmt, la, s);
+    cur ^= 1;
+  }
+  ea.nc = nc;
+  ea.NCB = ncb;
+  ea.W = (const uint8_t *)n.w[L - 1];
+  ea.bias = n.b[L - 1];
+  ea.X = n.act[cur];
+  ea.NQ = n.NQ[L - 1];
+  return e == hipSuccess ? launch_last(n.fmt, ea, prop, false, s) : e;
+}
+
+// Cells [n0, n0 + nc) of a chemistry update, layer by layer.
+hipError_t run_chem_layers(chem_dnn *h, int64_t n0, int nc, int64_t ld, const double *T,
+                           const double *P, const double *Y, double *Y_out, double *T_out,
+                           double *omega, double inv_dt, uint32_t *n_bad, hipStream_t s) {
+  const LayerNet net{h->prec, h->L, h->n_cu, h->lR, h->lNQ, h->wpack, h->bias, h->act};
+  FirstArgs fa{};
+  fa.T = T;
+  fa.P = P;
+  fa.x = Y;
+  fa.ld = ld;
+  fa.n0 = n0;
+  fa.D = h->D;
+  fa.fc = h->fc;
+  fa.dc = h->dc;
+  LastArgs ea{};
+  ea.T = T;
+  ea.P = P;
+  ea.x = Y;
+  ea.Y_out = Y_out;
+  ea.T_out = T_out;
+  ea.omega = omega;
+  ea.n_bad = n_bad;
+  ea.ld = ld;
+  ea.n0 = n0;
+  ea.S = h->S;
+  ea.fc = h->fc;
+  ea.dc = h->dc;
+  ea.inv_dt = inv_dt;
+  ea.thermo = h->thermo;
+  return run_layers(net, fa, ea, nc, false, !h->layered, s);
+}
+
+// The layer-by-layer path over chunks of kChunk cells.
 int32_t run_layered(chem_dnn *h, int64_t n, int64_t ld, const double *T, const double *P,
                     const double *Y, double *Y_out, double *T_out, double *omega, double inv_dt,
                     uint32_t *n_bad, hipStream_t s) {
-  const int fmt = h->prec, L = h->L;   // 0 FP32, 1 BF16, 2 FP16
   // the chunk buffers lie inside the workspace
   const uint8_t *end = h->ws + h->ws_bytes;
   if (h->act[0] < h->ws || h->act[1] < h->act[0] || h->act[1] > end) return CHEM_DNN_EWORKSPACE;
   hipError_t e = hipSuccess;
-  for (int64_t n0 = 0; n0 < n && e == hipSuccess; n0 += kChunk) {
-    const int nc = (int)(n - n0 < kChunk ? n - n0 : kChunk);
-    const int ncb = (nc + 15) / 16;
-    FirstArgs fa{T, P, Y, ld, n0, nc, ncb, h->D, (const uint8_t *)h->wpack[0], h->bias[0], h->act[0],
-                 h->lR[0], h->lR[0], h->fc, h->dc, h->n_cu, 0, nullptr, nullptr, 0};
-    e = launch_first(fmt, fa, false, false, s);
-    int cur = 0;
-    for (int l = 1; l < L - 1 && e == hipSuccess; ++l) {
-      LayerArgs la{(const uint8_t *)h->wpack[l], h->bias[l], h->act[cur], h->act[cur ^ 1], h->lR[l],
-                   h->lNQ[l], ncb, h->lR[l], h->n_cu, nullptr, 0, 0};
-      e = launch_layer(fmt, la, s);
-      cur ^= 1;
-    }
-    if (e == hipSuccess) {
-      LastArgs ea{T, P, Y, Y_out, T_out, omega, n_bad, ld, n0, nc, ncb, h->S,
-                  (const uint8_t *)h->wpack[L - 1], h->bias[L - 1], h->act[cur], h->lNQ[L - 1],
-                  h->fc, h->dc, inv_dt, h->thermo, nullptr};
-      e = launch_last(fmt, ea, false, false, s);
-    }
-  }
+  for (int64_t n0 = 0; n0 < n && e == hipSuccess; n0 += kChunk)
+    e = run_chem_layers(h, n0, (int)(n - n0 < kChunk ? n - n0 : kChunk), ld, T, P, Y, Y_out, T_out,
+                        omega, inv_dt, n_bad, s);
   return hip_status(e);
 }
 
@@ -402,7 +490,11 @@ int32_t prop_plan(const chem_prop_desc *d, PropPlan *p) {
       p->w[l] = off;
       off = align_up(off + (size_t)p->lay.R[l] * 16 * p->lay.NQ[l] * p->lay.KS * p->lay.EB);
     }
-    p->act[0] = p->act[1] = 0;
+    p->chunk = chain_cells(d->precision, p->lay, CHEM_DNN_GELU_TANH, true);
+    for (int b = 0; b < 2; ++b) {
+      p->act[b] = off;
+      off = align_up(off + chain_act_bytes(p->lay, b, p->chunk));
+    }
     p->total = off;
     return CHEM_DNN_OK;
   }
@@ -457,6 +549,34 @@ hipError_t (*step_launch(const chem_dnn *h))(const StepArgs &, int, hipStream_t)
                                                  : h->lay.step;
 }
 
+int grid_for(const chem_dnn *h, int64_t ntiles) {
+  int64_t g = ntiles < h->n_cu ? ntiles : h->n_cu;
+  return (int)(g < 1 ? 1 : g);
+}
+
+// Cells at the end of a batch of n that run layer by layer (see chain_cells).
+int64_t chain_rest(int64_t n, int64_t round, int64_t limit, int prec) {
+  const int64_t rest = n % round;
+  if (n >= round) limit = prec == CHEM_DNN_FP32 ? limit * 2 / 3 : limit / 2;
+  return rest <= limit ? rest : 0;
+}
+
+// The fused kernel over whole rounds of its tiles, the layer-by-layer kernels
+// over the rest of the batch where that is small.
+int32_t run_fused(chem_dnn *h, StepArgs a, hipStream_t s) {
+  const int64_t nc = chain_rest(a.n, (int64_t)h->n_cu * h->lay.MC, h->chain, h->prec), n = a.n - nc;
+  hipError_t e = hipSuccess;
+  if (n > 0) {
+    a.n = n;
+    a.ntiles = (n + h->lay.MC - 1) / h->lay.MC;
+    e = step_launch(h)(a, grid_for(h, a.ntiles), s);
+  }
+  if (nc && e == hipSuccess)
+    e = run_chem_layers(h, n, (int)nc, a.ld, a.T, a.P, a.Y, a.Y_out, a.T_out, a.omega, a.inv_dt,
+                        a.n_bad, s);
+  return hip_status(e);
+}
+
 // A handle made without training (max_batch = 0) sets the training kernels'
 // attributes with its first training call.
 int32_t tile_ready(chem_dnn *h) {
@@ -476,11 +596,6 @@ int32_t tiled_step(chem_dnn *h, int64_t B, int64_t ld, const double *T, const do
   const double c1 = 1.0 / (1.0 - pow(0.9, (double)step)), c2 = 1.0 / (1.0 - pow(0.999, (double)step));
   return hip_status(tile_train_step(h->widths, B, ld, T, P, Y, target, params, grads, adam_m, adam_v,
                                     lr, (float)c1, (float)c2, loss, h->fc, h->dc, t, h->n_cu, s));
-}
-
-int grid_for(const chem_dnn *h, int64_t ntiles) {
-  int64_t g = ntiles < h->n_cu ? ntiles : h->n_cu;
-  return (int)(g < 1 ? 1 : g);
 }
 
 }  // namespace
@@ -531,7 +646,9 @@ int32_t chem_dnn_init(const chem_dnn_desc *d, const float *params, void *workspa
   const bool layered = lay.prepare == nullptr;
   // the static scratch of the allocation-free training step (fused shapes)
   if (!layered && (st = scratch_init(dev)) != CHEM_DNN_OK) return st;
-  if ((layered ? layered_prepare() : lay.prepare()) != hipSuccess) return CHEM_DNN_EHIP;
+  const int64_t chain = layered ? 0 : chain_cells(d->precision, lay, d->gelu_form, false);
+  if (!layered && lay.prepare() != hipSuccess) return CHEM_DNN_EHIP;
+  if ((layered || chain) && layered_prepare(d->precision) != hipSuccess) return CHEM_DNN_EHIP;
   const bool tiled = !layered && tile_shape(d->widths);
   if (d->max_batch > 0 && (tiled ? tile_prepare_all() : train_prepare()) != hipSuccess)
     return CHEM_DNN_EHIP;
@@ -550,18 +667,18 @@ int32_t chem_dnn_init(const chem_dnn_desc *d, const float *params, void *workspa
       h->lR[l] = l == h->L - 1 ? 2 : d->widths[l + 1] / 16;
       h->lNQ[l] = (l == 0 ? 32 : d->widths[l]) / ks;
     }
+  } else {
+    for (int l = 0; l < 4; ++l) h->lR[l] = lay.R[l], h->lNQ[l] = lay.NQ[l];
   }
+  h->chain = chain;
   h->prec = d->precision;
   h->lay = lay;
   h->dev = dev;
   h->n_cu = n_cu;
   h->ws = (uint8_t *)workspace;
   h->ws_bytes = workspace_bytes;
-  if (layered) {
-    // (workspace pointers: only once h->ws is set)
-    h->act[0] = h->ws + p.act[0];
-    h->act[1] = h->ws + p.act[1];
-  }
+  h->act[0] = h->ws + p.act[0];
+  h->act[1] = h->ws + p.act[1];
   h->fc = (float *)(h->ws + p.fc);
   h->gtab = (float *)(h->ws + p.gtab);
   h->dc = (double *)(h->ws + p.dc);
@@ -658,7 +775,7 @@ int32_t chem_dnn_step(chem_dnn *h, int64_t n, int64_t ld, const double *T, const
   if (h->layered)
     return run_layered(h, n, ld, T, P, Y, Y_out, T_out, nullptr, 0.0, n_bad, (hipStream_t)stream);
   StepArgs a = step_args(h, n, ld, T, P, Y, Y_out, T_out, n_bad);
-  return hip_status(step_launch(h)(a, grid_for(h, a.ntiles), (hipStream_t)stream));
+  return run_fused(h, a, (hipStream_t)stream);
 }
 
 int32_t chem_dnn_step_source(chem_dnn *h, int64_t n, int64_t ld, const double *T,
@@ -677,7 +794,7 @@ int32_t chem_dnn_step_source(chem_dnn *h, int64_t n, int64_t ld, const double *T
   StepArgs a = step_args(h, n, ld, T, P, Y, Y_out, T_out, n_bad);
   a.omega = omega;
   a.inv_dt = 1.0 / dt;
-  return hip_status(step_launch(h)(a, grid_for(h, a.ntiles), (hipStream_t)stream));
+  return run_fused(h, a, (hipStream_t)stream);
 }
 
 int32_t chem_dnn_calibrate(chem_dnn *h, int64_t n, int64_t ld, const double *T, const double *P,
@@ -825,7 +942,7 @@ int32_t chem_dnn_debug_layers(chem_dnn *h, int64_t n, int64_t ld, const double *
   const int nc = (int)n, ncb = (nc + 15) / 16;
   FirstArgs fa{T, P, Y, ld, 0, nc, ncb, h->D, (const uint8_t *)h->wpack[0], h->bias[0], h->act[0],
                h->lR[0], h->lR[0], h->fc, h->dc, h->n_cu, 0, qin, acc, h->widths[1]};
-  hipError_t e = launch_first(fmt, fa, false, true, s);
+  hipError_t e = launch_first(fmt, fa, false, false, true, s);
   int cur = 0;
   for (int l = 1; l < L && e == hipSuccess; ++l) {
     // layer l's input, then the layer
@@ -839,7 +956,7 @@ int32_t chem_dnn_debug_layers(chem_dnn *h, int64_t n, int64_t ld, const double *
     } else {
       LastArgs ea{T, P, Y, nullptr, nullptr, nullptr, nullptr, ld, 0, nc, ncb, h->S,
                   (const uint8_t *)h->wpack[l], h->bias[l], h->act[cur], h->lNQ[l], h->fc, h->dc,
-                  0.0, 0, la_acc};
+                  0.0, 0, 0, la_acc};
       e = launch_last(fmt, ea, false, true, s);
     }
     cur ^= 1;
@@ -869,7 +986,8 @@ int32_t chem_prop_init(const chem_prop_desc *d, const float *params, void *works
   int dev = 0, n_cu = 0;
   st = current_device(&dev, &n_cu);
   if (st) return st;
-  if ((p.fused ? p.lay.prepare() : layered_prepare()) != hipSuccess) return CHEM_DNN_EHIP;
+  if (p.fused && p.lay.prepare() != hipSuccess) return CHEM_DNN_EHIP;
+  if (p.chunk && layered_prepare(d->precision) != hipSuccess) return CHEM_DNN_EHIP;
   chem_prop *h = new (std::nothrow) chem_prop();
   if (!h) return CHEM_DNN_EHIP;
   h->L = d->n_layers;
@@ -880,8 +998,8 @@ int32_t chem_prop_init(const chem_prop_desc *d, const float *params, void *works
   for (int l = 0; l <= h->L; ++l) h->widths[l] = d->widths[l];
   const int ks = ks_of(d->precision);
   for (int l = 0; l < h->L; ++l) {
-    h->lR[l] = l == h->L - 1 ? 2 : d->widths[l + 1] / 16;
-    h->lNQ[l] = (l == 0 ? 32 : d->widths[l]) / ks;
+    h->lR[l] = p.fused ? p.lay.R[l] : l == h->L - 1 ? 2 : d->widths[l + 1] / 16;
+    h->lNQ[l] = p.fused ? p.lay.NQ[l] : (l == 0 ? 32 : d->widths[l]) / ks;
   }
   h->chunk = p.chunk;
   h->ws = (uint8_t *)workspace;
@@ -892,10 +1010,8 @@ int32_t chem_prop_init(const chem_prop_desc *d, const float *params, void *works
     h->bias[l] = (float *)(h->ws + p.bias[l]);
     h->wpack[l] = h->ws + p.w[l];
   }
-  if (!h->fused) {
-    h->act[0] = h->ws + p.act[0];
-    h->act[1] = h->ws + p.act[1];
-  }
+  h->act[0] = h->ws + p.act[0];
+  h->act[1] = h->ws + p.act[1];
   memset(h->hfc, 0, sizeof(h->hfc));
   for (int l = 0; l < 4; ++l) {
     h->hfc[FConst::ASCALE + l] = h->hfc[FConst::INV_SA + l] = 1.0f;
@@ -942,11 +1058,15 @@ int32_t chem_prop_eval(chem_prop *h, int64_t n, int64_t ld, const double *x, dou
     if (x0 < y1 && y0 < x1) return CHEM_DNN_EINVAL;
   }
   hipStream_t s = (hipStream_t)stream;
-  if (h->fused) {
+  // fused: whole rounds of the fused kernel's tiles, and a small rest layer by layer
+  int64_t n0 = 0;
+  hipError_t e = hipSuccess;
+  if (h->fused) n0 = n - chain_rest(n, (int64_t)h->n_cu * h->lay.MC, h->chunk, h->prec);
+  if (n0 > 0) {
     StepArgs a{};
-    a.n = n;
+    a.n = n0;
     a.ld = ld;
-    a.ntiles = (n + h->lay.MC - 1) / h->lay.MC;
+    a.ntiles = (n0 + h->lay.MC - 1) / h->lay.MC;
     for (int l = 0; l < 4; ++l) { a.w[l] = h->wpack[l]; a.b[l] = h->bias[l]; }
     a.fc = h->fc;
     a.dc = h->pc;
@@ -954,30 +1074,23 @@ int32_t chem_prop_eval(chem_prop *h, int64_t n, int64_t ld, const double *x, dou
     a.y = y;
     a.D = D;
     a.K = K;
-    const int64_t grid = a.ntiles < h->n_cu ? a.ntiles : h->n_cu;
-    return hip_status(h->lay.step(a, (int)(grid < 1 ? 1 : grid), s));
+    e = h->lay.step(a, (int)(a.ntiles < h->n_cu ? a.ntiles : h->n_cu), s);
   }
-  const int L = h->L;
-  hipError_t e = hipSuccess;
-  for (int64_t n0 = 0; n0 < n && e == hipSuccess; n0 += h->chunk) {
-    const int nc = (int)(n - n0 < h->chunk ? n - n0 : h->chunk);
-    const int ncb = (nc + 15) / 16;
-    FirstArgs fa{nullptr, nullptr, x, ld, n0, nc, ncb, D, (const uint8_t *)h->wpack[0], h->bias[0],
-                 h->act[0], h->lR[0], h->lR[0], nullptr, h->pc, h->n_cu, 0, nullptr, nullptr, 0};
-    e = launch_first(h->prec, fa, true, false, s);
-    int cur = 0;
-    for (int l = 1; l < L - 1 && e == hipSuccess; ++l) {
-      LayerArgs la{(const uint8_t *)h->wpack[l], h->bias[l], h->act[cur], h->act[cur ^ 1], h->lR[l],
-                   h->lNQ[l], ncb, h->lR[l], h->n_cu, nullptr, 0, 0};
-      e = launch_layer(h->prec, la, s);
-      cur ^= 1;
-    }
-    if (e == hipSuccess) {
-      LastArgs ea{nullptr, nullptr, nullptr, y, nullptr, nullptr, nullptr, ld, n0, nc, ncb, K,
-                  (const uint8_t *)h->wpack[L - 1], h->bias[L - 1], h->act[cur], h->lNQ[L - 1],
-                  nullptr, h->pc, 0.0, 0, nullptr};
-      e = launch_last(h->prec, ea, true, false, s);
-    }
+  const LayerNet net{h->prec, h->L, h->n_cu, h->lR, h->lNQ, h->wpack, h->bias, h->act};
+  FirstArgs fa{};
+  fa.x = x;
+  fa.ld = ld;
+  fa.D = D;
+  fa.dc = h->pc;
+  LastArgs ea{};
+  ea.Y_out = y;
+  ea.ld = ld;
+  ea.S = K;
+  ea.dc = h->pc;
+  ea.shift = h->fused ? 2 : 0;
+  for (; n0 < n && e == hipSuccess; n0 += h->chunk) {
+    fa.n0 = ea.n0 = n0;
+    e = run_layers(net, fa, ea, (int)(n - n0 < h->chunk ? n - n0 : h->chunk), true, false, s);
   }
   return hip_status(e);
 }

@@ -117,6 +117,7 @@ struct LastArgs {
   const double *dc;
   double inv_dt;
   int thermo;
+  int shift;             // property networks: output k on row k + shift
   float *dbg_acc;        // debug mode: accumulators [S][nc]
 };
 // Property networks: FP64 constants of the input and output affine maps.
@@ -129,9 +130,10 @@ struct PConst {
     N = 128
   };
 };
-// fmt: 0 FP32, 1 BF16, 2 FP16 operands; prop: property network; dbg: layer dump
-hipError_t layered_prepare();
-hipError_t launch_first(int fmt, const FirstArgs &a, bool prop, bool dbg, hipStream_t s);
+// fmt: 0 FP32, 1 BF16, 2 FP16 operands; prop: property network; fused: feature
+// rounding of the fused kernel; dbg: layer dump
+hipError_t layered_prepare(int fmt);
+hipError_t launch_first(int fmt, const FirstArgs &a, bool prop, bool fused, bool dbg, hipStream_t s);
 hipError_t launch_layer(int fmt, const LayerArgs &a, hipStream_t s);
 hipError_t launch_last(int fmt, const LastArgs &a, bool prop, bool dbg, hipStream_t s);
 // debug: hidden layer with its accumulators dumped; the operand values of B

@@ -13,6 +13,9 @@
 //
 // each writing the next layer's B fragments.
 //
+// Batches of the fused networks too small to fill the chip with the fused
+// kernel's tiles run through the same kernels, on its packed weights.
+//
 // The property networks of the supercritical flame (PRNet, Sec. 2 and the
 // network sizes of Sec. 4: 3-1024-512-256-1 and 3-2048-1024-512-4) run on the
 // same kernels with their own input and output maps (Z-score of the input
@@ -339,8 +342,11 @@ __global__ __launch_bounds__(T::NT, 1) void layer_kernel(LayerArgs a) {
 // over memory: 32,768 cells x 2048 rows in BF16 take 40 us (67 M GELUs take 25
 // us of issue, the 134 MB written 27), with a feature kernel before it and the
 // layer on the tiled kernel 43 us; 1,000 cells 7 against 15 us.
+//
+// FUSED: the features are rounded as in the fused kernel (T, P and the species
+// of their slots through FP32), for its networks' small batches.
 constexpr int FWCB = 2;
-template <class Op, bool PROP, bool DBG = false>
+template <class Op, bool PROP, bool FUSED, bool DBG = false>
 __global__ __launch_bounds__(256) void first_kernel(FirstArgs a) {
   using frag_t = typename Op::frag_t;
   constexpr int NQ = 32 / Op::KS, NE = 16 / Op::EB, RPQ = Op::KS / 16;
@@ -380,9 +386,16 @@ __global__ __launch_bounds__(256) void first_kernel(FirstArgs a) {
       } else {
         z = Op::feature(ypow(in[j], a.fc[FConst::LAM]), a.fc[FConst::ZA + f], a.fc[FConst::ZC + f]);
         if (j < 2) {
-          const elem_t tp = Op::feature((in[j] - a.dc[j == 0 ? DConst::T_MU : DConst::P_MU]) *
-                                        a.dc[j == 0 ? DConst::T_IS : DConst::P_IS]);
-          z = g == 0 ? tp : z;
+          const double tp = (in[j] - a.dc[j == 0 ? DConst::T_MU : DConst::P_MU]) *
+                            a.dc[j == 0 ? DConst::T_IS : DConst::P_IS];
+          if constexpr (FUSED) {
+            float zf = __builtin_fmaf(ypow(in[j], a.fc[FConst::LAM]), a.fc[FConst::ZA + f], a.fc[FConst::ZC + f]);
+            zf = g == 0 ? (float)tp : zf;
+            asm("" : "+v"(zf));
+            z = (elem_t)zf;
+          } else {
+            z = g == 0 ? Op::feature(tp) : z;
+          }
         }
       }
       z = used ? z : (elem_t)0.0f;
@@ -442,8 +455,8 @@ __global__ __launch_bounds__(256) void first_kernel(FirstArgs a) {
 // The output layer (32 rows) and what follows it, a wave per cell-block: the
 // accumulators of its lanes are the rows 16 h + 4 g + r of cell cl, which the
 // chemistry networks' post-processing takes as it does in the fused kernel
-// (post.inc; output rows shifted by two), the property networks' (PROP,
-// unshifted) as y = o sigma + mu in FP64.  Weights and activations go straight
+// (post.inc; output rows shifted by two), the property networks' (PROP) as
+// y = o sigma + mu in FP64.  Weights and activations go straight
 // to registers, PF k-steps ahead (the weights of a workgroup's four waves
 // come through its L1).  Bound by the state's and the activations' loads and
 // by the FP64 post-processing, whose four lanes per cell run it in a quarter
@@ -506,7 +519,7 @@ __global__ __launch_bounds__(256) void last_kernel(LastArgs a) {
     for (int h = 0; h < 2; ++h)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int s = 16 * h + 4 * g + r - (PROP ? 0 : 2);
+        const int s = 16 * h + 4 * g + r - 2;
         if (valid && s >= 0 && s < a.S) a.dbg_acc[(size_t)s * a.nc + cell] = o[h][r];
       }
   } else if constexpr (PROP) {
@@ -515,8 +528,8 @@ __global__ __launch_bounds__(256) void last_kernel(LastArgs a) {
     for (int h = 0; h < 2; ++h)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int k = 16 * h + 4 * g + r;
-        if (k < a.S)
+        const int k = 16 * h + 4 * g + r - a.shift;
+        if (k >= 0 && k < a.S)
           a.Y_out[(int64_t)k * a.ld + i] =
               __builtin_fma((double)o[h][r], a.dc[PConst::OUT_SD + k], a.dc[PConst::OUT_MU + k]);
       }
@@ -649,11 +662,8 @@ template <class Op> static hipError_t prepare_op() {
   static_assert(T128::LDS <= 65536 && T64::LDS <= 65536 && T32::LDS <= 65536 && T16::LDS <= 65536, "LDS");
   return e;
 }
-hipError_t layered_prepare() {
-  hipError_t e = prepare_op<OpF32>();
-  if (e == hipSuccess) e = prepare_op<OpBF16>();
-  if (e == hipSuccess) e = prepare_op<OpF16>();
-  return e;
+hipError_t layered_prepare(int fmt) {
+  return fmt == 0 ? prepare_op<OpF32>() : fmt == 1 ? prepare_op<OpBF16>() : prepare_op<OpF16>();
 }
 
 hipError_t launch_layer(int fmt, const LayerArgs &a, hipStream_t s) {
@@ -667,7 +677,7 @@ hipError_t launch_layer(int fmt, const LayerArgs &a, hipStream_t s) {
 
 namespace {
 
-template <class Op> hipError_t launch_first_op(const FirstArgs &a0, bool prop, bool dbg, hipStream_t s) {
+template <class Op> hipError_t launch_first_op(const FirstArgs &a0, bool prop, bool fused, bool dbg, hipStream_t s) {
   FirstArgs a = a0;
   // row-blocks per wave: few enough that about 16 waves per CU have work, at
   // most 32 (features recomputed once per 32 row-blocks cost nothing any more)
@@ -676,7 +686,9 @@ template <class Op> hipError_t launch_first_op(const FirstArgs &a0, bool prop, b
   a.RPW = (int)(rpw < 4 ? 4 : rpw > 32 ? 32 : rpw);
   const int64_t waves = groups * ((a.RO + a.RPW - 1) / a.RPW);
   const dim3 grid((unsigned)((waves + 3) / 4));
-  auto k = prop ? first_kernel<Op, true> : dbg ? first_kernel<Op, false, true> : first_kernel<Op, false>;
+  auto k = prop ? first_kernel<Op, true, false>
+           : fused ? first_kernel<Op, false, true>
+           : dbg ? first_kernel<Op, false, false, true> : first_kernel<Op, false, false>;
   hipLaunchKernelGGL(k, grid, dim3(256), 0, s, a);
   return hipGetLastError();
 }
@@ -688,11 +700,11 @@ template <class Op> hipError_t launch_last_op(const LastArgs &a, bool prop, bool
 
 }  // namespace
 
-hipError_t launch_first(int fmt, const FirstArgs &a, bool prop, bool dbg, hipStream_t s) {
+hipError_t launch_first(int fmt, const FirstArgs &a, bool prop, bool fused, bool dbg, hipStream_t s) {
   switch (fmt) {
-    case 0: return launch_first_op<OpF32>(a, prop, dbg, s);
-    case 1: return launch_first_op<OpBF16>(a, prop, dbg, s);
-    case 2: return launch_first_op<OpF16>(a, prop, dbg, s);
+    case 0: return launch_first_op<OpF32>(a, prop, fused, dbg, s);
+    case 1: return launch_first_op<OpBF16>(a, prop, fused, dbg, s);
+    case 2: return launch_first_op<OpF16>(a, prop, fused, dbg, s);
     default: return hipErrorInvalidValue;
   }
 }
