@@ -564,6 +564,8 @@ int64_t chain_rest(int64_t n, int64_t round, int64_t limit, int prec) {
 // The fused kernel over whole rounds of its tiles, the layer-by-layer kernels
 // over the rest of the batch where that is small.
 int32_t run_fused(chem_dnn *h, StepArgs a, hipStream_t s) {
+  // the small network's own kernel has slots for 18 species
+  if (h->lay.small && h->gelu_form == CHEM_DNN_GELU_TANH && h->S <= 18) return hip_status(h->lay.small(a, h->n_cu, s));
   const int64_t nc = chain_rest(a.n, (int64_t)h->n_cu * h->lay.MC, h->chain, h->prec), n = a.n - nc;
   hipError_t e = hipSuccess;
   if (n > 0) {
@@ -648,6 +650,7 @@ int32_t chem_dnn_init(const chem_dnn_desc *d, const float *params, void *workspa
   if (!layered && (st = scratch_init(dev)) != CHEM_DNN_OK) return st;
   const int64_t chain = layered ? 0 : chain_cells(d->precision, lay, d->gelu_form, false);
   if (!layered && lay.prepare() != hipSuccess) return CHEM_DNN_EHIP;
+  if (lay.small && lay.small_prepare() != hipSuccess) return CHEM_DNN_EHIP;
   if ((layered || chain) && layered_prepare(d->precision) != hipSuccess) return CHEM_DNN_EHIP;
   const bool tiled = !layered && tile_shape(d->widths);
   if (d->max_batch > 0 && (tiled ? tile_prepare_all() : train_prepare()) != hipSuccess)

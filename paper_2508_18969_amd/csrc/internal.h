@@ -157,6 +157,9 @@ struct NetLayout {
   hipError_t (*calib_tab16)(const StepArgs &, int grid, hipStream_t);
   hipError_t (*dbg)(const StepArgs &, int grid, hipStream_t);    // layer dump
   hipError_t (*prepare)();     // one-time function attributes
+  // the small network: its own kernel for the tanh form
+  hipError_t (*small)(const StepArgs &, int n_cu, hipStream_t);
+  hipError_t (*small_prepare)();
 };
 // The same for the kernel's property mode (hidden widths h1, h2, h3); only
 // `step` and `prepare` are set.

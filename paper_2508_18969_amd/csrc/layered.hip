@@ -538,6 +538,11 @@ __global__ __launch_bounds__(256) void last_kernel(LastArgs a) {
     const double *const dcl = a.dc;
     const float *const fcl = a.fc;
     const float lam = fcl[FConst::LAM], inv_lam = fcl[FConst::INV_LAM];
+    // (row offsets: a uniform part and one product per lane)
+#define POST_SLOTS 8
+#define POST_R(h) 4
+#define POST_ROW(h, r, g) (16 * (h) + 4 * (g) + (r))
+#define POST_AT(h, r, g, s) ((int64_t)(16 * (h) + (r) - 2) * a.ld + ((int64_t)(4 * (g)) * a.ld + i))
 #include "post.inc"
   }
 }

@@ -1,5 +1,5 @@
 // The fused chemistry-update kernel instantiated for FP32 operands.
-#include "step_kernel.h"
+#include "step_small.h"
 
 namespace chemdnn {
 
@@ -7,7 +7,7 @@ namespace chemdnn {
 // 29-species net (1600, 800, 400).
 bool find_layout_fp32(int h1, int h2, int h3, NetLayout *out) {
   if (h1 == 400 && h2 == 200 && h3 == 100) {
-    fill_layout<Cfg<OpF32, 2, 4, 400, 200, 100>, true>(out);
+    fill_small_layout<Cfg<OpF32, 2, 4, 400, 200, 100>, true, 2>(out);
     return true;
   }
   if (h1 == 1600 && h2 == 800 && h3 == 400) {

@@ -914,6 +914,10 @@ __global__ __launch_bounds__(C::NW * 64, 1) void chem_step_kernel(StepArgs a) {
         Yc[j] = y2[0];
         Yc[j + 1] = y2[1];
       }
+#define POST_SLOTS 8
+#define POST_R(h) 4
+#define POST_ROW(h, r, g) (16 * (h) + 4 * (g) + (r))
+#define POST_AT(h, r, g, s) ((int64_t)(s) * a.ld + i)
 #include "post.inc"
     }
   }
