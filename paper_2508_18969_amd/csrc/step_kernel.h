@@ -111,6 +111,16 @@ template <class Op_, int CB_, int NW_, int H1_, int H2_, int H3_> struct Cfg {
   static constexpr bool w4_lds(int gt) { return lds_w4(gt) + W4_BYTES <= 160 * 1024; }
   static constexpr int lds_bytes(int gt) { return lds_w4(gt) + (w4_lds(gt) ? W4_BYTES : 0); }
   static constexpr int LDS_BYTES = lds_bytes(0);
+  // FP8 with twice as many waves as cell-blocks: while the first CB waves
+  // post-process a tile (7 thousand cycles), the next CB transform the next
+  // one's inputs (5 thousand), into an A0 of its own behind the rest; the tanh
+  // form only.  31-1600-800-400-29 over 300,007 cells: 799 us with the
+  // transform after the post-processing, 756 so.  BF16 and FP16, bound by the
+  // matrix cores' power, do not change (3,160 us over 2^20 cells both ways),
+  // FP32 loses 2 % (3,270 to 3,335 us over 2^17).
+  static constexpr bool SPLIT = NW >= 2 * CB && FRAG == 32;
+  static constexpr int lds_split() { return LDS_BYTES + (SPLIT ? NQ1 * QBYTES : 0); }
+  static_assert(lds_split() <= 160 * 1024, "LDS budget");
   static_assert(lds_bytes(1) <= 160 * 1024 && lds_bytes(2) <= 160 * 1024, "LDS budget");
 };
 
@@ -188,7 +198,8 @@ __global__ __launch_bounds__(C::NW * 64, 1) void chem_step_kernel(StepArgs a) {
   using S3 = typename C::S3;
   constexpr int CB = C::CB, KS = C::KS, FRAG = C::FRAG, EB = C::EB, RPQ = C::RPQ;
   extern __shared__ __align__(16) uint8_t smem[];
-  uint8_t *const A0 = smem + C::LDS_A0;
+  constexpr bool SPLIT = C::SPLIT && GT == 0 && !CALIB && !DBG;
+  uint8_t *const A0 = smem + (SPLIT ? C::LDS_BYTES : C::LDS_A0);
   uint8_t *const A1 = smem + C::LDS_A1;
   uint8_t *const A2 = smem + C::LDS_A2;
   // the wave index is uniform: keeping it scalar lets every weight address be a
@@ -255,8 +266,12 @@ __global__ __launch_bounds__(C::NW * 64, 1) void chem_step_kernel(StepArgs a) {
   // from an opaque copy of the lane group: hoisted out of the tile loop they
   // would be spilled, and the reload of each - counted with the loads in issue
   // order - would make every load wait for the HBM load before it.
+  // the waves of the input transform (w itself, or the CB waves after the
+  // post-processing's)
+  const int wp = SPLIT ? w - CB : w;
+  const bool prew = SPLIT ? w >= CB && w < 2 * CB : C::NW == CB || w < CB;
   auto load_xin = [&](int64_t t) {
-    const int64_t i = t * C::MC + 16 * w + cl;
+    const int64_t i = t * C::MC + 16 * wp + cl;
     const int64_t ii = (t < a.ntiles && i < a.n) ? i : 0;
     const int go = opaque_v(g);
 #pragma unroll
@@ -271,7 +286,64 @@ __global__ __launch_bounds__(C::NW * 64, 1) void chem_step_kernel(StepArgs a) {
       }
     }
   };
-  if (C::NW == CB || w < CB) load_xin(blockIdx.x);
+  if (prew) load_xin(blockIdx.x);
+
+  auto put_state = [&]() {
+    // the state stays in LDS for the post-processing (the same lane then
+    // holds the same fields), instead of a second read from HBM
+    if constexpr (!CALIB && !PROP) {
+      double *st = (double *)(smem + C::LDS_ST) + (wp * 64 + lane) * 8;
+#pragma unroll
+      for (int j = 0; j < 8; j += 2) *(double2v *)(st + j) = double2v{xin[j], xin[j + 1]};
+    }
+  };
+  // Lane (cell 16 wp + cl, group g) computes input features f = 16h + 4g + r
+  // of tile t.
+  auto put_features = [&](int64_t t) {
+    const int64_t i = t * C::MC + 16 * wp + cl;
+    const bool valid = i < a.n;
+    f4 v[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        // selects instead of branches: feature f is T or P only in the
+        // first two slots of the lanes with g == 0
+        const int f = 16 * h + 4 * g + r;
+        const double x = xin[4 * h + r];
+        float z;
+        if constexpr (PROP) {
+          z = (float)((x - dcl[PConst::IN_MU + f]) * dcl[PConst::IN_IS + f]);
+          z = f < a.D ? z : 0.0f;
+        } else {
+          z = __builtin_fmaf(ypow(x, lam), fcl[FConst::ZA + f], fcl[FConst::ZC + f]);
+          z = f - 2 < a.S ? z : 0.0f;
+          if (h == 0 && r < 2) {
+            const float ztp = r == 0 ? (float)((x - dcl[DConst::T_MU]) * dcl[DConst::T_IS])
+                                     : (float)((x - dcl[DConst::P_MU]) * dcl[DConst::P_IS]);
+            z = g == 0 ? ztp : z;
+          }
+        }
+        z = valid ? z : 0.0f;
+        if (CALIB) amx[0] = umaxf(amx[0], __builtin_fabsf(z));
+        v[h][r] = z * inv_sa[0];
+        if constexpr (DBG)
+          if (valid && f < a.S + 2) a.dbg_in[(int64_t)(a.dbg_in_row[0] + f) * a.n + i] = Op::q(v[h][r]);
+      }
+    if constexpr (KS == 16) {
+      // two k-steps of 16: feature 16h + 4g + r sits in k-step h, slot r
+      Op::store4(A0 + ((0 * CB + wp) * 64 + lane) * FRAG, v[0]);
+      Op::store4(A0 + ((1 * CB + wp) * 64 + lane) * FRAG, v[1]);
+    } else {
+      uint8_t *p = A0 + (wp * 64 + lane) * FRAG;
+      Op::store4(p, v[0]);
+      Op::store4(p + 4 * EB, v[1]);
+      // slots 8.. (features >= 32) are zero padding
+#pragma unroll
+      for (int o = 8 * EB; o < FRAG; o += 4) *(uint32_t *)(p + o) = 0u;
+    }
+  };
+  if (SPLIT && prew) put_features(blockIdx.x);
 
   for (int64_t tile = blockIdx.x; tile < a.ntiles; tile += gridDim.x) {
     const int64_t cell0 = tile * C::MC;
@@ -284,64 +356,15 @@ __global__ __launch_bounds__(C::NW * 64, 1) void chem_step_kernel(StepArgs a) {
     const int voff = lane * (int)sizeof(frag_t);
 
     // ------------------------------------------------------------ preprocess
-    // Lane (cell 16w + cl, group g) computes input features f = 16h + 4g + r.
     // (Every wave has finished the previous tile's layer 4, which reads A2,
     // and post-processing, which reads the staged state, before the
     // preprocess overwrites both.)
     lds_barrier();
-    if (C::NW == CB || w < CB) {
-      const int64_t i = cell0 + 16 * w + cl;
-      // the state stays in LDS for the post-processing (the same lane then
-      // holds the same fields), instead of a second read from HBM
-      if constexpr (!CALIB && !PROP) {
-        double *st = (double *)(smem + C::LDS_ST) + (w * 64 + lane) * 8;
-#pragma unroll
-        for (int j = 0; j < 8; j += 2) *(double2v *)(st + j) = double2v{xin[j], xin[j + 1]};
-      }
-      const bool valid = i < a.n;
-      f4 v[2];
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          // selects instead of branches: feature f is T or P only in the
-          // first two slots of the lanes with g == 0
-          const int f = 16 * h + 4 * g + r;
-          const double x = xin[4 * h + r];
-          float z;
-          if constexpr (PROP) {
-            z = (float)((x - dcl[PConst::IN_MU + f]) * dcl[PConst::IN_IS + f]);
-            z = f < a.D ? z : 0.0f;
-          } else {
-            z = __builtin_fmaf(ypow(x, lam), fcl[FConst::ZA + f], fcl[FConst::ZC + f]);
-            z = f - 2 < a.S ? z : 0.0f;
-            if (h == 0 && r < 2) {
-              const float ztp = r == 0 ? (float)((x - dcl[DConst::T_MU]) * dcl[DConst::T_IS])
-                                       : (float)((x - dcl[DConst::P_MU]) * dcl[DConst::P_IS]);
-              z = g == 0 ? ztp : z;
-            }
-          }
-          z = valid ? z : 0.0f;
-          if (CALIB) amx[0] = umaxf(amx[0], __builtin_fabsf(z));
-          v[h][r] = z * inv_sa[0];
-          if constexpr (DBG)
-            if (valid && f < a.S + 2) a.dbg_in[(int64_t)(a.dbg_in_row[0] + f) * a.n + i] = Op::q(v[h][r]);
-        }
-      if constexpr (KS == 16) {
-        // two k-steps of 16: feature 16h + 4g + r sits in k-step h, slot r
-        Op::store4(A0 + ((0 * CB + w) * 64 + lane) * FRAG, v[0]);
-        Op::store4(A0 + ((1 * CB + w) * 64 + lane) * FRAG, v[1]);
-      } else {
-        uint8_t *p = A0 + (w * 64 + lane) * FRAG;
-        Op::store4(p, v[0]);
-        Op::store4(p + 4 * EB, v[1]);
-        // slots 8.. (features >= 32) are zero padding
-#pragma unroll
-        for (int o = 8 * EB; o < FRAG; o += 4) *(uint32_t *)(p + o) = 0u;
-      }
+    if (prew) {
+      put_state();
+      if constexpr (!SPLIT) put_features(tile);
     }
-    lds_barrier();
-
+    if constexpr (!SPLIT) lds_barrier();
 
     // Layer 1, super-chunk sc, in two steps: the products (into acc1) and the
     // activation of values [v0, v1) (bias + GELU + quantise into A1 buffer
@@ -781,7 +804,7 @@ __global__ __launch_bounds__(C::NW * 64, 1) void chem_step_kernel(StepArgs a) {
             // have gone out (loads complete in order: a weight load behind
             // it would wait for HBM), its address arithmetic beside the
             // remaining products
-            if (XIN_L3 && q == XQ && i == 0 && (C::NW == CB || w < CB)) load_xin(tile + gridDim.x);
+            if (XIN_L3 && q == XQ && i == 0 && prew) load_xin(tile + gridDim.x);
             __builtin_amdgcn_sched_barrier(0);
           }
 #pragma unroll
@@ -797,7 +820,7 @@ __global__ __launch_bounds__(C::NW * 64, 1) void chem_step_kernel(StepArgs a) {
     const bool vpost = ipost < a.n;
     // (single-buffered layer-3 loop, or fewer than two k-steps: the next
     // tile's state is fetched here, unless it comes after layer 4)
-    if (!LATE_XIN && !XIN_L3 && (C::NW == CB || w < CB)) load_xin(tile + gridDim.x);
+    if (!LATE_XIN && !XIN_L3 && prew) load_xin(tile + gridDim.x);
     lds_barrier();  // every wave is done reading the layer-2 activation
     {
 #pragma unroll
@@ -840,6 +863,10 @@ __global__ __launch_bounds__(C::NW * 64, 1) void chem_step_kernel(StepArgs a) {
     if (CALIB) continue;
 
     // ------------------------------------------------------------ layer 4 + post
+    if (SPLIT && prew && tile + gridDim.x < a.ntiles) {
+      if constexpr (LATE_XIN) load_xin(tile + gridDim.x);
+      put_features(tile + gridDim.x);
+    }
     if (w < CB) {
       f4 o[2];
 #pragma unroll
@@ -864,7 +891,7 @@ __global__ __launch_bounds__(C::NW * 64, 1) void chem_step_kernel(StepArgs a) {
           for (int rb = 0; rb < 2; ++rb) o[rb] = Op::mma(w4r[rb][q], af, o[rb]);
         }
       }
-      if constexpr (LATE_XIN) load_xin(tile + gridDim.x);
+      if constexpr (LATE_XIN && !SPLIT) load_xin(tile + gridDim.x);
       if constexpr (DBG) {
         // output row rho = 16 h + 4 g + r holds species rho - 2
 #pragma unroll
@@ -937,7 +964,7 @@ __global__ __launch_bounds__(C::NW * 64, 1) void chem_step_kernel(StepArgs a) {
 template <class C, int GT, bool PROP = false>
 static hipError_t launch_step(const StepArgs &a, int grid, hipStream_t s) {
   hipLaunchKernelGGL((chem_step_kernel<C, false, GT, PROP>), dim3(grid), dim3(C::NW * 64),
-                     C::lds_bytes(GT), s, a);
+                     GT == 0 ? C::lds_split() : C::lds_bytes(GT), s, a);
   return hipGetLastError();
 }
 template <class C, int GT>
@@ -955,7 +982,8 @@ static hipError_t launch_dbg(const StepArgs &a, int grid, hipStream_t s) {
 template <class C, bool CALIB, int GT, bool PROP = false, bool DBG = false>
 static hipError_t set_lds_limit() {
   return hipFuncSetAttribute((const void *)chem_step_kernel<C, CALIB, GT, PROP, DBG>,
-                             hipFuncAttributeMaxDynamicSharedMemorySize, C::lds_bytes(GT));
+                             hipFuncAttributeMaxDynamicSharedMemorySize,
+                             GT == 0 ? C::lds_split() : C::lds_bytes(GT));
 }
 template <class C, bool WITH_CALIB>
 static hipError_t prepare() {
