@@ -31,7 +31,7 @@
 // 9.8 thousand, half of them the post-processing's 1,000 instructions in one
 // wave.  16 / 4,096 / 16,384 / 262,144 cells, fused and here, us: BF16 16.1 /
 // 17.0 / 17.9 / 199 and 8.7 / 10.0 / 15.8 / 155; FP8 16.5 / 17 / 31 / 289 and
-// 8.8 / 9.9 / 14.9 / 142; FP32 28.7 / 30.6 / 57 / 808 and 18.3 / 20.4 / 47 / 642
+// 8.8 / 9.9 / 14.9 / 142; FP32 28.7 / 30.6 / 57 / 808 and 17.3 / 19.4 / 47 / 642
 // (FP32 is bound by the matrix cores: 12.8 thousand cycles of layer 2 alone on
 // the SIMD with four row-blocks).
 #pragma once
@@ -68,7 +68,9 @@ template <class C_, int CB_> struct Small {
   static constexpr int LDS_A2 = LDS_A1 + K2 * CB * FB;
   static constexpr int LDS_BYTES = LDS_A2 + K3 * CB * FB;
   static_assert(LDS_BYTES <= 160 * 1024, "LDS budget");
-  static constexpr int PF = 6;                       // FP32: layer-2 k-steps in flight
+  // FP32: layer-2 k-steps in flight (one block of 4,096 cells: six 20.7 us, eight
+  // 19.4, ten 19.7, twelve spill and take 21.7; two blocks are bound by products)
+  static constexpr int PF = CB == 1 ? 8 : 6;
 };
 
 template <class S>
@@ -125,9 +127,9 @@ __global__ __launch_bounds__(S::NW * 64, 2) void small_step_kernel(StepArgs a) {
   // weights of layers 2 and 3 (packed row-blocks of C::NQ2 / C::NQ3 k-steps)
   const int rb2b = low ? 8 + w : 12, rb3 = w < S::RB3 ? w : S::RB3 - 1;
   frag_t w2[2][S::STREAM ? PF : K2], w3[K3], w1[S::STREAM ? 4 : 1][NQ1];
-  auto load_w2 = [&](int u, int q) {
+  auto load_w2 = [&](int u, int q, bool second) {
     w2[0][u] = ldb_frag<frag_t>(W2, w * C::NQ2 + q, voff);
-    w2[1][u] = ldb_frag<frag_t>(W2, rb2b * C::NQ2 + q, voff);
+    if (second) w2[1][u] = ldb_frag<frag_t>(W2, rb2b * C::NQ2 + q, voff);
   };
   auto load_w3 = [&]() {
 #pragma unroll
@@ -160,7 +162,7 @@ __global__ __launch_bounds__(S::NW * 64, 2) void small_step_kernel(StepArgs a) {
     load_w1();
   } else {
 #pragma unroll
-    for (int q = 0; q < K2; ++q) load_w2(q, q);
+    for (int q = 0; q < K2; ++q) load_w2(q, q, true);
     for (int i = threadIdx.x; i < S::RB1 * NQ1 * FB / 16; i += NT)
       ((i4 *)(smem + S::LDS_W1))[i] = ((const i4 *)a.w[0])[i];
   }
@@ -289,9 +291,15 @@ __global__ __launch_bounds__(S::NW * 64, 2) void small_step_kernel(StepArgs a) {
   for (int64_t tile = blockIdx.x; tile < a.ntiles; tile += gridDim.x, buf ^= 1) {
     renew();
     // ------------------------------------------------------------ layer 1
-    if constexpr (S::STREAM)
+    if constexpr (S::STREAM) {
+      if (low || pre) {
 #pragma unroll
-      for (int u = 0; u < PF; ++u) load_w2(u, u);
+        for (int u = 0; u < PF; ++u) load_w2(u, u, true);
+      } else {
+#pragma unroll
+        for (int u = 0; u < PF; ++u) load_w2(u, u, false);
+      }
+    }
     {
       frag_t xq[NQ1][CB];
 #pragma unroll
@@ -363,7 +371,7 @@ __global__ __launch_bounds__(S::NW * 64, 2) void small_step_kernel(StepArgs a) {
             for (int u = 0; u < PF; ++u) {
               kstep(q0 + u, u);
               const int qn = q0 + u + PF;
-              load_w2(u, qn < K2 ? qn : K2 - 1);
+              load_w2(u, qn < K2 ? qn : K2 - 1, KIND() > 0);
             }
 #pragma unroll
           for (int u = 0; u < K2 - NF; ++u) kstep(NF + u, u);
