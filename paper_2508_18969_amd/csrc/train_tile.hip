@@ -854,23 +854,34 @@ struct FinishArgs {
 
 // The gradient: 64 outputs per workgroup, its four waves sum a quarter of the
 // splits each in increasing order, the quarters in wave order; then Adam on
-// the sum.  The last workgroup sums the loss (one wave, fixed order, FP64).
+// the sum.  The last workgroup sums the loss (fixed order, FP64).  Bound by the
+// latency of the loads, so several of each lane's are in flight together (one
+// after the other, and one wave for the loss: 12.6 us at 65,536 samples; so 7).
 __global__ __launch_bounds__(256) void finish_kernel(FinishArgs a) {
   __shared__ float q[4][64];
   const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int64_t o = blockIdx.x * (int64_t)64 + l;
   if (blockIdx.x * (int64_t)64 >= a.np) {
-    if (w == 0) {
-      double s = 0.0;
-      for (int64_t i = l; i < a.nl; i += 64) s += (double)a.lpart[i];
-      if (a.loss)
-        for (int64_t i = l; i < a.chunk; i += 64) s += a.closs[i];
+    // (the loss: all four waves, eight loads of each lane in flight)
+    __shared__ double qs[4];
+    double s = 0.0;
+    for (int64_t i0 = threadIdx.x; i0 < a.nl; i0 += 8 * 256) {
+      float v[8];
 #pragma unroll
-      for (int k = 32; k >= 1; k >>= 1) s += __shfl_xor(s, k);
-      if (l == 0) {
-        if (a.loss) *a.loss = (float)(s / a.denom);
-        else a.closs[a.chunk] = s;
-      }
+      for (int u = 0; u < 8; ++u) v[u] = i0 + 256 * u < a.nl ? a.lpart[i0 + 256 * u] : 0.0f;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += (double)v[u];
+    }
+    if (a.loss)
+      for (int64_t i = threadIdx.x; i < a.chunk; i += 256) s += a.closs[i];
+#pragma unroll
+    for (int k = 32; k >= 1; k >>= 1) s += __shfl_xor(s, k);
+    if (l == 0) qs[w] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      s = ((qs[0] + qs[1]) + qs[2]) + qs[3];
+      if (a.loss) *a.loss = (float)(s / a.denom);
+      else a.closs[a.chunk] = s;
     }
     return;
   }
@@ -879,7 +890,13 @@ __global__ __launch_bounds__(256) void finish_kernel(FinishArgs a) {
   const int zq = (ns + 3) / 4, z0 = w * zq, z1 = z0 + zq < ns ? z0 + zq : ns;
   float acc = 0.0f;
   if (valid)
-    for (int z = z0; z < z1; ++z) acc += a.part[(int64_t)z * a.np + o];
+    for (int z = z0; z < z1; z += 4) {
+      float v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = a.part[(int64_t)(z + u < z1 ? z + u : z1 - 1) * a.np + o];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) acc = z + u < z1 ? acc + v[u] : acc;
+    }
   q[w][l] = acc;
   __syncthreads();
   if (w == 0 && valid) {
