@@ -331,17 +331,20 @@ __global__ __launch_bounds__(T::NT, 1) void layer_kernel(LayerArgs a) {
 }
 
 // ------------------------------------------------------------------ first layer
-// The first hidden layer with its input: a wave computes the features of
-// FWCB cell-blocks straight into the B fragments of its lanes (lane: cell cl,
-// group g holds the features frag_feature(KS, q, g, j)) - power transform and
-// Z-score for the chemistry networks, Z-score in FP64 for the property
-// networks (PROP), zero past the inputs and for cells past the chunk - then
-// RPW row-blocks of the layer.  Its 32 inputs are one or two k-steps, so there
-// is nothing to stage: bound by the GELUs and by the writes.  The row parts of
-// a cell group recompute its features, which replaces a launch and a pass
-// over memory: 32,768 cells x 2048 rows in BF16 take 40 us (67 M GELUs take 25
-// us of issue, the 134 MB written 27), with a feature kernel before it and the
-// layer on the tiled kernel 43 us; 1,000 cells 7 against 15 us.
+// The first hidden layer with its input.  A workgroup's four waves compute the
+// features of FWCB cell-blocks, two slots of every lane each, into the B
+// fragments (lane: cell cl, group g holds the features frag_feature(KS, q, g,
+// j)) in LDS - power transform and Z-score for the chemistry networks, Z-score
+// in FP64 for the property networks (PROP), zero past the inputs and for cells
+// past the chunk - then RPW row-blocks of the layer each.  Its 32 inputs are
+// one or two k-steps, so there is nothing else to stage: bound by the GELUs
+// and by the writes.  The workgroups of a cell group recompute its features,
+// which replaces a launch and a pass over memory: 32,768 cells x 2048 rows in
+// BF16 take 40 us (67 M GELUs take 25 us of issue, the 134 MB written 27), with
+// a feature kernel before it and the layer on the tiled kernel 43 us.  With
+// every wave computing all its features, 4,096 cells x 1600 rows took 11.3 us
+// (now 9.0), 30,011 x 2048 of a property network 37.5 (33.5), 1,000 x 2048 7.1
+// (6.4), 16 x 1600 4.3 (3.7).
 //
 // FUSED: the features are rounded as in the fused kernel (T, P and the species
 // of their slots through FP32), for its networks' small batches.
@@ -350,23 +353,25 @@ template <class Op, bool PROP, bool FUSED, bool DBG = false>
 __global__ __launch_bounds__(256) void first_kernel(FirstArgs a) {
   using frag_t = typename Op::frag_t;
   constexpr int NQ = 32 / Op::KS, NE = 16 / Op::EB, RPQ = Op::KS / 16;
+  __shared__ __align__(16) uint8_t feat[FWCB * NQ * FB];
   const int lane = threadIdx.x & 63, g = lane >> 4, cl = lane & 15;
-  const int id = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int parts = (a.RO + a.RPW - 1) / a.RPW;
-  const int r0 = id % parts * a.RPW, cb0 = id / parts * FWCB;
-  if (cb0 >= a.NCB) return;
+  const int v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // a workgroup: four row parts of one cell group
+  const int parts = (a.RO + a.RPW - 1) / a.RPW, quads = (parts + 3) / 4;
+  const int r0 = (blockIdx.x % quads * 4 + v) * a.RPW, cb0 = blockIdx.x / quads * FWCB;
   const int r1 = r0 + a.RPW < a.RO ? r0 + a.RPW : a.RO;
   const rsrc_t Wr = layer_rsrc(a.W, (uint32_t)a.R * NQ * FB);
-  frag_t x[FWCB][NQ];
+  // slots 2 v and 2 v + 1 of every lane
+  const int f0 = 16 * (v >> 1) + 4 * g + 2 * (v & 1);
 #pragma unroll
   for (int c = 0; c < FWCB; ++c) {
     const int cell = 16 * (cb0 + c) + cl;
     const bool valid = cell < a.nc;
     const int64_t i = a.n0 + (valid ? cell : 0);
-    double in[8];
+    double in[2];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int f = 16 * (j >> 2) + 4 * g + (j & 3);
+    for (int j = 0; j < 2; ++j) {
+      const int f = f0 + j;
       if constexpr (PROP) {
         in[j] = a.x[(int64_t)(f < a.D ? f : a.D - 1) * a.ld + i];
       } else {
@@ -375,21 +380,22 @@ __global__ __launch_bounds__(256) void first_kernel(FirstArgs a) {
       }
     }
     typedef decltype(Op::feature(0.0)) elem_t;
-    __attribute__((aligned(16))) elem_t buf[8];
+    __attribute__((aligned(8))) elem_t buf[2];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int f = 16 * (j >> 2) + 4 * g + (j & 3);
+    for (int j = 0; j < 2; ++j) {
+      const int f = f0 + j;
       const bool used = valid && f < a.D;
       elem_t z;
       if constexpr (PROP) {
         z = Op::feature((in[j] - a.dc[PConst::IN_MU + f]) * a.dc[PConst::IN_IS + f]);
       } else {
-        z = Op::feature(ypow(in[j], a.fc[FConst::LAM]), a.fc[FConst::ZA + f], a.fc[FConst::ZC + f]);
-        if (j < 2) {
+        const float u = ypow(in[j], a.fc[FConst::LAM]), za = a.fc[FConst::ZA + f], zc = a.fc[FConst::ZC + f];
+        z = Op::feature(u, za, zc);
+        if (v == 0) {
           const double tp = (in[j] - a.dc[j == 0 ? DConst::T_MU : DConst::P_MU]) *
                             a.dc[j == 0 ? DConst::T_IS : DConst::P_IS];
           if constexpr (FUSED) {
-            float zf = __builtin_fmaf(ypow(in[j], a.fc[FConst::LAM]), a.fc[FConst::ZA + f], a.fc[FConst::ZC + f]);
+            float zf = __builtin_fmaf(u, za, zc);
             zf = g == 0 ? (float)tp : zf;
             asm("" : "+v"(zf));
             z = (elem_t)zf;
@@ -400,12 +406,20 @@ __global__ __launch_bounds__(256) void first_kernel(FirstArgs a) {
       }
       z = used ? z : (elem_t)0.0f;
       if constexpr (DBG)
-        if (used && r0 == 0) a.dbg_in[(size_t)f * a.nc + cell] = (float)z;
+        if (used && blockIdx.x % quads == 0) a.dbg_in[(size_t)f * a.nc + cell] = (float)z;
       buf[j] = z;
     }
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) x[c][q] = *(const frag_t *)(buf + q * NE);
+    uint8_t *const p = feat + (c * NQ + 2 * v / NE) * FB + lane * 16 + 2 * v % NE * Op::EB;
+    if constexpr (Op::EB == 2) *(uint32_t *)p = *(const uint32_t *)buf;
+    else *(uint64_t *)p = *(const uint64_t *)buf;
   }
+  __syncthreads();
+  if (r0 >= a.RO) return;
+  frag_t x[FWCB][NQ];
+#pragma unroll
+  for (int c = 0; c < FWCB; ++c)
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) x[c][q] = *(const frag_t *)(feat + (c * NQ + q) * FB + lane * 16);
   auto load = [&](frag_t (&wf)[RPQ][NQ], f4 (&b)[RPQ], int rb) {
 #pragma unroll
     for (int k = 0; k < RPQ; ++k) {
@@ -685,12 +699,13 @@ namespace {
 template <class Op> hipError_t launch_first_op(const FirstArgs &a0, bool prop, bool fused, bool dbg, hipStream_t s) {
   FirstArgs a = a0;
   // row-blocks per wave: few enough that about 16 waves per CU have work, at
-  // most 32 (features recomputed once per 32 row-blocks cost nothing any more)
+  // most 32; the row parts in whole fours, a workgroup's waves
   const int64_t groups = (a.NCB + FWCB - 1) / FWCB;
-  int64_t rpw = groups * a.RO / (16 * (int64_t)a.n_cu) / 2 * 2;
-  a.RPW = (int)(rpw < 4 ? 4 : rpw > 32 ? 32 : rpw);
-  const int64_t waves = groups * ((a.RO + a.RPW - 1) / a.RPW);
-  const dim3 grid((unsigned)((waves + 3) / 4));
+  const int64_t rpw = groups * a.RO / (16 * (int64_t)a.n_cu), r = rpw < 4 ? 4 : rpw > 32 ? 32 : rpw;
+  const int64_t quads = (a.RO + 2 * r) / (4 * r), q = quads < 1 ? 1 : quads;
+  a.RPW = (int)((a.RO + 8 * q - 1) / (8 * q) * 2);
+  const int64_t parts = (a.RO + a.RPW - 1) / a.RPW;
+  const dim3 grid((unsigned)(groups * ((parts + 3) / 4)));
   auto k = prop ? first_kernel<Op, true, false>
            : fused ? first_kernel<Op, false, true>
            : dbg ? first_kernel<Op, false, false, true> : first_kernel<Op, false, false>;
