@@ -157,9 +157,11 @@ struct NetLayout {
   hipError_t (*calib_tab16)(const StepArgs &, int grid, hipStream_t);
   hipError_t (*dbg)(const StepArgs &, int grid, hipStream_t);    // layer dump
   hipError_t (*prepare)();     // one-time function attributes
-  // the small network: its own kernel for the tanh form
-  hipError_t (*small)(const StepArgs &, int n_cu, hipStream_t);
-  hipError_t (*small_prepare)();
+  // the tanh form for up to pick_species species, where it has several kernels
+  // or tiles to choose from by the batch's size; or null
+  hipError_t (*pick)(const StepArgs &, int n_cu, hipStream_t);
+  hipError_t (*pick_prepare)();
+  int pick_species;
 };
 // The same for the kernel's property mode (hidden widths h1, h2, h3); only
 // `step` and `prepare` are set.

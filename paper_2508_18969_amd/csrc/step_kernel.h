@@ -65,17 +65,22 @@ template <class Op_, int CB_, int NW_, int H1_, int H2_, int H3_> struct Cfg {
   static constexpr int H2N = padN(H2_, CB_, FRAG == 32 && NW_ <= 4, NW_), H3N = padN(H3_, CB_, FRAG == 32 && NW_ <= 4, NW_);
   static constexpr int H2P = roundup(H2N, KS), H3P = roundup(H3N, KS);
   static constexpr int R1 = H1P / 16, R2 = H2N / 16, R3 = H3N / 16, R4 = 2;
-  static constexpr int NQ2 = H1P / KS, NQ3 = H2P / KS, NQ4 = H3P / KS;
-  static constexpr int NSC = H1P / SC, RB1W = SC / 64, QSC = SC / KS, RPQ = KS / 16;
+  // 48-cell tiles on eight waves (CB3) compute more padding rows than 64-cell
+  // ones, but the same k-steps: both read the same packed weights
+  static constexpr bool CB3 = CB_ == 3 && NW_ == 8;
+  static constexpr int NQ2 = H1P / KS, NQ3 = CB3 ? roundup(H2_, KS) / KS : H2P / KS,
+                       NQ4 = CB3 ? roundup(H3_, KS) / KS : H3P / KS;
+  static constexpr int NSC = H1P / SC, RB1W = CB3 && SC > 64 ? SC / 128 : SC / 64, QSC = SC / KS, RPQ = KS / 16;
   using S2 = Split<R2, CB_, NW_>;
   using S3 = Split<R3, CB_, NW_>;
   static constexpr int QBYTES = CB * 64 * FRAG;     // one k-step of a tile's activations
   static constexpr int NW1 = RB1W * NQ1;             // layer-1 fragments per wave per chunk
   // A chunk's layer-1 tiles: SC / 16 / RB1W row groups x CB cell-blocks.  With
   // more waves than row groups, the waves of a row group split its
-  // cell-blocks (CBW each).
+  // cell-blocks (CBW each), or the first ones compute them where they do not
+  // split.
   static constexpr int L1G = SC / 16 / RB1W;
-  static constexpr int CBW = NW_ > L1G ? CB_ * L1G / NW_ : CB_;
+  static constexpr int CBW = NW_ > L1G && CB_ * L1G % NW_ == 0 ? CB_ * L1G / NW_ : CB_;
   static constexpr int NBIAS = H1P + H2N + H3N + 32; // biases of all layers, FP32
   static constexpr int LDS_BIAS = 0;
   static constexpr int LDS_DC = roundup(NBIAS * 4, 16);          // DConst or PConst block (FP64)
@@ -96,7 +101,7 @@ template <class Op_, int CB_, int NW_, int H1_, int H2_, int H3_> struct Cfg {
   static constexpr int A01_BYTES = NQ1 * QBYTES + 2 * LA * QSC * QBYTES;
   static constexpr int NW2 = S2::F + S2::NREM;               // layer-2 fragments per wave per k-step
   static constexpr int NB2 = NW_ > 4 ? 1 : QSC % 2 == 0 ? 2 : 1;   // layer-2 register buffers
-  static constexpr int A2_BYTES = Max<NQ3, NQ4>::v * QBYTES;
+  static constexpr int A2_BYTES = Max<H2P, H3P>::v / KS * QBYTES;
   // The LDS tail holds the GELU table (tabulated form only), then the
   // output-layer weights, copied once per workgroup when they fit.
   static constexpr int W4_BYTES = R4 * NQ4 * 64 * FRAG;
@@ -1038,6 +1043,19 @@ static void fill_prop_layout(NetLayout *L) {
   L->lds_bytes = C::LDS_BYTES;
   L->step = launch_step<C, 0, true>;
   L->prepare = prepare_prop<C>;
+}
+
+// Tiles of 64 (CL) or 48 cells (CS) by the batch's size: the fewer nanoseconds
+// of first + rounds * per.
+struct TileTime { int first, per; };
+template <class CL, class CS, bool PROP>
+static hipError_t launch_by_size(const StepArgs &a0, int n_cu, TileTime l, TileTime s, hipStream_t st) {
+  auto rounds = [&](int mc) { return ((a0.n + mc - 1) / mc + n_cu - 1) / n_cu; };
+  const bool small = s.first + rounds(CS::MC) * s.per < l.first + rounds(CL::MC) * l.per;
+  StepArgs a = a0;
+  a.ntiles = (a.n + (small ? CS::MC : CL::MC) - 1) / (small ? CS::MC : CL::MC);
+  const int grid = (int)(a.ntiles < n_cu ? a.ntiles : n_cu);
+  return small ? launch_step<CS, 0, PROP>(a, grid, st) : launch_step<CL, 0, PROP>(a, grid, st);
 }
 
 }  // namespace chemdnn

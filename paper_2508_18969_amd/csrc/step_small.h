@@ -491,8 +491,9 @@ template <class C, int MAXCB> static hipError_t small_prepare() {
 }
 template <class C, bool WITH_CALIB, int MAXCB> static void fill_small_layout(NetLayout *L) {
   fill_layout<C, WITH_CALIB>(L);
-  L->small = small_step<C, MAXCB>;
-  L->small_prepare = small_prepare<C, MAXCB>;
+  L->pick = small_step<C, MAXCB>;
+  L->pick_prepare = small_prepare<C, MAXCB>;
+  L->pick_species = 18;                              // its slots
 }
 
 }  // namespace chemdnn

@@ -58,3 +58,16 @@ def test_property_rests_give_the_same_bits(prec):
         assert torch.equal(bits(h.eval(x[:, :n].contiguous())), bits(yb[:, :n])), n
     y2 = h.eval(torch.cat([x, x[:, :37]], 1).contiguous())
     assert torch.equal(bits(y2), bits(torch.cat([yb, yb[:, :37]], 1)))
+
+
+def test_fp8_tiles_give_the_same_bits():
+    """FP8 chooses tiles of 64 or 48 cells by the batch's size: edges of both
+    tiles and of the ranges against a batch in tiles of 64."""
+    net = synth.make_net(2, bias_scale=0.1, out_stats=True)
+    h = make_handle(net, "fp8", thermo=synth.make_thermo(2, 29), act_amax=[6.0, 4.0, 4.0, 4.0])
+    T, P, Y = dev_state(synth.make_state(2, 2 * BIG))
+    Yb, Tb = h.step(T, P, Y)
+    for n in (1, 47, 48, 49, 63, 65, 1000, 12288, 12289, 16384, 16385, 24577):
+        print(f"case fp8 tiles n={n}", flush=True)
+        Yn, Tn = h.step(T[:n].clone(), P[:n].clone(), Y[:, :n].contiguous())
+        assert torch.equal(bits(Yn), bits(Yb[:, :n])) and torch.equal(bits(Tn), bits(Tb[:n])), n
