@@ -33,7 +33,7 @@ STATE_BYTES_PER_CELL = 8 * (2 + 29) + 8 * (29 + 1)                       # in + 
 PEAK_TFLOPS = {"fp32": 157.3, "bf16": 2500.0, "fp16": 2500.0, "fp8": 5000.0}
 HBM_PEAK_GBS = 8000.0
 KERNEL_SOURCES = ["paper_2508_18969_amd/csrc/step_kernel.h", "paper_2508_18969_amd/csrc/step_bf16.hip",
-                  "paper_2508_18969_amd/csrc/common.h"]
+                  "paper_2508_18969_amd/csrc/post.inc", "paper_2508_18969_amd/csrc/common.h"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_chem_step_bf16_2p20.json")
 BLOCK_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_chem_step_block_2p27.json")
 

@@ -112,7 +112,9 @@ typedef struct {
 } chem_dnn_desc;
 
 /* Bytes of device workspace chem_dnn_init needs for `desc` (packed weights,
- * biases, scales, constants and, if max_batch > 0, training scratch).
+ * biases, scales, constants, activation buffers where layers run one by one
+ * - other networks than the fused ones, and small batches of the larger of
+ * these - and, if max_batch > 0, training scratch).
  * EINVAL for a bad description, EUNSUPPORTED for a shape the library does not compile. */
 int32_t chem_dnn_workspace_bytes(const chem_dnn_desc *desc, size_t *bytes);
 
@@ -170,8 +172,9 @@ int32_t chem_dnn_get_scales(chem_dnn *h, float *act_scale, float *w_scale, void 
  * pre-trained ODENet); it does not describe how the network is trained.  The
  * entry points below are this library's own differentiable path for
  * training or fine-tuning the chemistry network on labels from a stiff
- * integrator: an FP32 forward that saves (or recomputes) the hidden
- * pre-activations, an MSE loss on the normalised Box-Cox increment, a
+ * integrator: an FP32 forward (of the 17-species shape as products of
+ * three-part BF16 splits, 24 bits, summed in FP32) that saves (or recomputes)
+ * the hidden pre-activations, an MSE loss on the normalised Box-Cox increment, a
  * hand-written backward of the tanh-form GELU network and Adam (Kingma & Ba,
  * Algorithm 1).  Fused network shapes only.
  * ------------------------------------------------------------------------ */

@@ -157,7 +157,7 @@ int eb_of(int prec) { return prec == CHEM_DNN_FP32 ? 4 : 2; }
 // / 93 and 27 / 41 / 63 / 88.  Networks below 1 MiB are not worth four
 // launches (19-400-200-100-17 in BF16 at 1,000 cells: 16.6 against 17.1).  A
 // property network's buffers keep to the workspace slack that its description
-// allows in 16 bits (256 cells: 23.6 us fused, 15.5 layer by layer).
+// allows in 16 bits (256 cells: 22.2 us fused, 15.5 layer by layer).
 // FP8 and the tabulated GELU have no layer kernels.
 // Behind whole rounds the layer kernels have to wait for the last fused tile,
 // while a fused rest starts on the CUs that are done: there the limit is
