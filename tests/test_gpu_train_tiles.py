@@ -8,7 +8,7 @@ import pytest
 
 import synth
 from oracle import train
-from tests.helpers import make_handle
+from tests.helpers import dev_state, make_handle
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -88,3 +88,38 @@ def test_gradients_are_no_further_off_than_fp32_products():
     got, ref = train.unflatten(gp.cpu().numpy().astype(np.float64), WIDTHS), train.unflatten(g_ref, WIDTHS)
     for a, b in zip(got[0] + got[1], ref[0] + ref[1]):
         assert _rel(a, b) <= 5e-7
+
+
+def test_first_training_call_under_capture():
+    """A handle made without training sets its training kernels up with its
+    first training call; that call may be the one that is captured."""
+    net = synth.make_net(4)
+    n = 300
+    st = synth.make_state(4, n)
+    h = make_handle(net, "fp32", max_batch=0)
+    T, P, Y = dev_state(st)
+    target = 0.1 * torch.randn(17, n, device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+    start = h._params.clone()
+    p, g, m, v = start.clone(), torch.empty_like(start), torch.zeros_like(start), torch.zeros_like(start)
+    loss = torch.empty(1, device="cuda")
+
+    def step():
+        return h.train_step_noalloc(T, P, Y, target, p, g, m, v, 1, loss=loss)
+
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step()
+    seen = []
+    for k in range(4):                      # three replays, then the eager call
+        p.copy_(start)
+        m.zero_()
+        v.zero_()
+        g.fill_(-1.0)
+        loss.fill_(-1.0)
+        graph.replay() if k < 3 else step()
+        torch.cuda.synchronize()
+        seen.append([t.clone() for t in (p, g, m, v, loss)])
+    for s in seen[:3]:
+        assert all(torch.equal(a, b) for a, b in zip(s, seen[3]))
+    assert float(seen[3][4]) > 0.0
