@@ -94,6 +94,7 @@ template <int WRB_, int WR_, int WCB_, int WC_, int ST_, int KG_> struct Tile {
 };
 using T256 = Tile<4, 4, 8, 2, 4, 1>;   // 256 x 256, eight waves of 64 x 128
 using T128 = Tile<2, 4, 4, 2, 4, 1>;   // 128 x 128, eight waves of 32 x 64
+using T128S = Tile<2, 4, 4, 1, 8, 1>;  // 128 x 64, four waves of 32 x 64
 using T64 = Tile<2, 2, 2, 2, 4, 2>;    // 64 x 64, four waves of 32 x 32
 using T32 = Tile<2, 1, 2, 2, 4, 2>;    // 32 x 64, two waves of 32 x 32
 using T16 = Tile<2, 1, 1, 1, 8, 2>;    // 32 x 16, one wave
@@ -594,9 +595,10 @@ hipError_t launch_tile(const LayerArgs &a, hipStream_t s) {
 }
 
 // The tile of a hidden layer.  A launch of G workgroups puts c = ceil(G / CUs)
-// of them on the fullest CU; a k-step then takes about max(lat, c thr) ns,
-// where lat is a lone workgroup's k-step (waits, barrier and the products of
-// one wave) and thr its share of a full CU (products, LDS and L2 reads).
+// of them on the fullest CU; a k-step then takes about lat ns for c = 1 and
+// c thr for more, where lat is the k-step of one workgroup per CU (waits,
+// barrier and products) and thr its share of a CU with several (products, LDS
+// and L2 reads).
 // Measured on the layers of 19-2048-4096-2048-1024-512-17 at 16 to 32,768 cells
 // (lat from 16 cells, thr from the largest sizes of each tile).  The small
 // tiles fill the chip for small chunks, the large ones read each operand
@@ -604,20 +606,23 @@ hipError_t launch_tile(const LayerArgs &a, hipStream_t s) {
 // workgroups of 256 x 256 and 26 us on 512 of 64 x 64; at 32,768 cells 450 us
 // against 940 us.
 struct TileCost { int trb, tcb, lat, thr; };
-constexpr TileCost kCost16[5] = {{T256::TRB, T256::TCB, 580, 870}, {T128::TRB, T128::TCB, 210, 270},
+// 128 x 64 tiles (16 bits) are for the launches that they fill in one round:
+// 4096 -> 2048 over 1,000 cells 23.5 us on 256 of them, 26.3 on 512 of 64 x 64.
+constexpr TileCost kCost16[6] = {{T256::TRB, T256::TCB, 870, 870}, {T128::TRB, T128::TCB, 270, 270},
                                  {T64::TRB, T64::TCB, 96, 92}, {T32::TRB, T32::TCB, 94, 70},
-                                 {T16::TRB, T16::TCB, 77, 50}};
+                                 {T16::TRB, T16::TCB, 77, 50}, {T128S::TRB, T128S::TCB, 178, 215}};
 constexpr TileCost kCost32[5] = {{T256::TRB, T256::TCB, 3540, 3540}, {T128::TRB, T128::TCB, 920, 910},
                                  {T64::TRB, T64::TCB, 280, 245}, {T32::TRB, T32::TCB, 275, 230},
                                  {T16::TRB, T16::TCB, 165, 110}};
-int pick_tile(const TileCost (&cost)[5], const LayerArgs &a) {
+template <int N>
+int pick_tile(const TileCost (&cost)[N], const LayerArgs &a) {
   int best = 0;
   int64_t tb = INT64_MAX;
-  for (int k = 0; k < 5; ++k) {
+  for (int k = 0; k < N; ++k) {
     const int64_t G = (int64_t)((a.R + cost[k].trb - 1) / cost[k].trb) *
                       ((a.NCB + cost[k].tcb - 1) / cost[k].tcb);
-    const int64_t c = (G + a.n_cu - 1) / a.n_cu, t = c * cost[k].thr;
-    const int64_t u = t > cost[k].lat ? t : cost[k].lat;
+    const int64_t c = (G + a.n_cu - 1) / a.n_cu;
+    const int64_t u = c > 1 ? c * cost[k].thr : cost[k].lat;
     if (u < tb) tb = u, best = k;
   }
   return best;
@@ -625,24 +630,36 @@ int pick_tile(const TileCost (&cost)[5], const LayerArgs &a) {
 
 template <class Op>
 hipError_t launch_layer_op(const LayerArgs &a, hipStream_t s) {
-  switch (pick_tile(Op::EB == 4 ? kCost32 : kCost16, a)) {
+  int k;
+  if constexpr (Op::EB == 4) k = pick_tile(kCost32, a);
+  else k = pick_tile(kCost16, a);
+  switch (k) {
     case 0: return launch_tile<Op, T256>(a, s);
     case 1: return launch_tile<Op, T128>(a, s);
     case 2: return launch_tile<Op, T64>(a, s);
     case 3: return launch_tile<Op, T32>(a, s);
-    default: return launch_tile<Op, T16>(a, s);
+    case 4: return launch_tile<Op, T16>(a, s);
+    default:
+      if constexpr (Op::EB == 2) return launch_tile<Op, T128S>(a, s);
+      return hipErrorInvalidValue;
   }
 }
 
 // the layer dump: the same tiles with the accumulators written out
 template <class Op>
 hipError_t launch_layer_dbg_op(const LayerArgs &a, hipStream_t s) {
-  switch (pick_tile(Op::EB == 4 ? kCost32 : kCost16, a)) {
+  int k;
+  if constexpr (Op::EB == 4) k = pick_tile(kCost32, a);
+  else k = pick_tile(kCost16, a);
+  switch (k) {
     case 0: return launch_tile<Op, T256, true>(a, s);
     case 1: return launch_tile<Op, T128, true>(a, s);
     case 2: return launch_tile<Op, T64, true>(a, s);
     case 3: return launch_tile<Op, T32, true>(a, s);
-    default: return launch_tile<Op, T16, true>(a, s);
+    case 4: return launch_tile<Op, T16, true>(a, s);
+    default:
+      if constexpr (Op::EB == 2) return launch_tile<Op, T128S, true>(a, s);
+      return hipErrorInvalidValue;
   }
 }
 
@@ -678,6 +695,10 @@ template <class Op, class T, bool DBG = false> static hipError_t prepare_tile() 
 template <class Op> static hipError_t prepare_op() {
   hipError_t e = prepare_tile<Op, T256>();   // (the other tiles: at most 64 KiB)
   if (e == hipSuccess) e = prepare_tile<Op, T256, true>();
+  if constexpr (Op::EB == 2) {
+    if (e == hipSuccess) e = prepare_tile<Op, T128S>();
+    if (e == hipSuccess) e = prepare_tile<Op, T128S, true>();
+  }
   static_assert(T128::LDS <= 65536 && T64::LDS <= 65536 && T32::LDS <= 65536 && T16::LDS <= 65536, "LDS");
   return e;
 }
