@@ -564,13 +564,13 @@ int64_t chain_rest(int64_t n, int64_t round, int64_t limit, int prec) {
 // The fused kernel over whole rounds of its tiles, the layer-by-layer kernels
 // over the rest of the batch where that is small.
 int32_t run_fused(chem_dnn *h, StepArgs a, hipStream_t s) {
-  const bool pick = h->lay.pick && h->gelu_form == CHEM_DNN_GELU_TANH && h->S <= h->lay.pick_species;
+  const auto pick = h->S <= h->lay.pick_species ? h->lay.pick[h->gelu_form] : nullptr;
   const int64_t nc = chain_rest(a.n, (int64_t)h->n_cu * h->lay.MC, h->chain, h->prec), n = a.n - nc;
   hipError_t e = hipSuccess;
   if (n > 0) {
     a.n = n;
     a.ntiles = (n + h->lay.MC - 1) / h->lay.MC;
-    e = pick ? h->lay.pick(a, h->n_cu, s) : step_launch(h)(a, grid_for(h, a.ntiles), s);
+    e = pick ? pick(a, h->n_cu, s) : step_launch(h)(a, grid_for(h, a.ntiles), s);
   }
   if (nc && e == hipSuccess)
     e = run_chem_layers(h, n, (int)nc, a.ld, a.T, a.P, a.Y, a.Y_out, a.T_out, a.omega, a.inv_dt,
@@ -649,7 +649,7 @@ int32_t chem_dnn_init(const chem_dnn_desc *d, const float *params, void *workspa
   if (!layered && (st = scratch_init(dev)) != CHEM_DNN_OK) return st;
   const int64_t chain = layered ? 0 : chain_cells(d->precision, lay, d->gelu_form, false);
   if (!layered && lay.prepare() != hipSuccess) return CHEM_DNN_EHIP;
-  if (lay.pick && lay.pick_prepare() != hipSuccess) return CHEM_DNN_EHIP;
+  if (lay.pick[d->gelu_form] && lay.pick_prepare[d->gelu_form]() != hipSuccess) return CHEM_DNN_EHIP;
   if ((layered || chain) && layered_prepare(d->precision) != hipSuccess) return CHEM_DNN_EHIP;
   const bool tiled = !layered && tile_shape(d->widths);
   if (d->max_batch > 0 && (tiled ? tile_prepare_all() : train_prepare()) != hipSuccess)
@@ -989,7 +989,7 @@ int32_t chem_prop_init(const chem_prop_desc *d, const float *params, void *works
   st = current_device(&dev, &n_cu);
   if (st) return st;
   if (p.fused && p.lay.prepare() != hipSuccess) return CHEM_DNN_EHIP;
-  if (p.fused && p.lay.pick && p.lay.pick_prepare() != hipSuccess) return CHEM_DNN_EHIP;
+  if (p.fused && p.lay.pick[0] && p.lay.pick_prepare[0]() != hipSuccess) return CHEM_DNN_EHIP;
   if (p.chunk && layered_prepare(d->precision) != hipSuccess) return CHEM_DNN_EHIP;
   chem_prop *h = new (std::nothrow) chem_prop();
   if (!h) return CHEM_DNN_EHIP;
@@ -1077,8 +1077,8 @@ int32_t chem_prop_eval(chem_prop *h, int64_t n, int64_t ld, const double *x, dou
     a.y = y;
     a.D = D;
     a.K = K;
-    e = h->lay.pick ? h->lay.pick(a, h->n_cu, s)
-                    : h->lay.step(a, (int)(a.ntiles < h->n_cu ? a.ntiles : h->n_cu), s);
+    e = h->lay.pick[0] ? h->lay.pick[0](a, h->n_cu, s)
+                       : h->lay.step(a, (int)(a.ntiles < h->n_cu ? a.ntiles : h->n_cu), s);
   }
   const LayerNet net{h->prec, h->L, h->n_cu, h->lR, h->lNQ, h->wpack, h->bias, h->act};
   FirstArgs fa{};

@@ -157,10 +157,11 @@ struct NetLayout {
   hipError_t (*calib_tab16)(const StepArgs &, int grid, hipStream_t);
   hipError_t (*dbg)(const StepArgs &, int grid, hipStream_t);    // layer dump
   hipError_t (*prepare)();     // one-time function attributes
-  // the tanh form for up to pick_species species, where it has several kernels
-  // or tiles to choose from by the batch's size; or null
-  hipError_t (*pick)(const StepArgs &, int n_cu, hipStream_t);
-  hipError_t (*pick_prepare)();
+  // per GELU form (0 tanh, 1 FP32 table, 2 FP16 table), for up to pick_species
+  // species: the launch that chooses among several kernels or tiles by the
+  // batch's size, or null
+  hipError_t (*pick[3])(const StepArgs &, int n_cu, hipStream_t);
+  hipError_t (*pick_prepare[3])();
   int pick_species;
 };
 // The same for the kernel's property mode (hidden widths h1, h2, h3); only

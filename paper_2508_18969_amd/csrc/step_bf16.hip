@@ -29,10 +29,10 @@ bool find_prop_layout_bf16(int h1, int h2, int h3, NetLayout *out) {
     static_assert(Large::R2 == Small::R2 && Large::R3 == Small::R3 && Large::NQ3 == Small::NQ3 &&
                   Large::NQ4 == Small::NQ4, "one packed layout");
     fill_prop_layout<Large>(out);
-    out->pick = [](const StepArgs &a, int n_cu, hipStream_t s) {
+    out->pick[0] = [](const StepArgs &a, int n_cu, hipStream_t s) {
       return launch_by_size<Large, Small, true>(a, n_cu, {7400, 21600}, {8200, 18600}, s);
     };
-    out->pick_prepare = prepare_prop<Small>;
+    out->pick_prepare[0] = prepare_prop<Small>;
     return true;
   }
   return false;

@@ -23,10 +23,10 @@ bool find_layout_fp8(int h1, int h2, int h3, NetLayout *out) {
   }
   if (h1 == 1600 && h2 == 800 && h3 == 400) {
     fill_layout<Small29, false>(out);
-    out->pick = [](const StepArgs &a, int n_cu, hipStream_t s) {
+    out->pick[0] = [](const StepArgs &a, int n_cu, hipStream_t s) {
       return launch_by_size<Large29, Small29, false>(a, n_cu, {16000, 39000}, {12000, 32000}, s);
     };
-    out->pick_prepare = [] { return set_lds_limit<Large29, false, 0>(); };
+    out->pick_prepare[0] = [] { return set_lds_limit<Large29, false, 0>(); };
     out->pick_species = 30;
     return true;
   }

@@ -33,16 +33,18 @@
 // 17.0 / 17.9 / 199 and 8.7 / 10.0 / 15.8 / 155; FP8 16.5 / 17 / 31 / 289 and
 // 8.8 / 9.9 / 14.9 / 142; FP32 28.7 / 30.6 / 57 / 808 and 17.3 / 19.4 / 47 / 642
 // (FP32 is bound by the matrix cores: 12.8 thousand cycles of layer 2 alone on
-// the SIMD with four row-blocks).
+// the SIMD with four row-blocks); BF16 with the FP32 table 27.4 / 28.5 / 29.5 /
+// 375 and 10.3 / 11.8 / 20.1 / 211.
 #pragma once
 #include "step_kernel.h"
 
 namespace chemdnn {
 
-// C: the fused kernel's configuration (packed layout) of the same network.
-template <class C_, int CB_> struct Small {
+// C: the fused kernel's configuration (packed layout) of the same network; GT:
+// the hidden activation - 0 the tanh form, 1 the FP32 table, 2 the FP16 table.
+template <class C_, int CB_, int GT_> struct Small {
   using C = C_;
-  static constexpr int CB = CB_, NW = 8, MC = 16 * CB;
+  static constexpr int CB = CB_, NW = 8, MC = 16 * CB, GT = GT_;
   static constexpr int FRAG = C::FRAG, RPQ = C::RPQ, FB = 64 * FRAG;
   static constexpr bool STREAM = C::EB == 4;         // FP32: weights from L2
   // row-blocks with rows of the network, and k-steps that hold any
@@ -66,7 +68,8 @@ template <class C_, int CB_> struct Small {
   static constexpr int LDS_A3 = LDS_A1;
   static_assert(K4 < K2, "the zero rows of layer 2's input stay");
   static constexpr int LDS_A2 = LDS_A1 + K2 * CB * FB;
-  static constexpr int LDS_BYTES = LDS_A2 + K3 * CB * FB;
+  static constexpr int LDS_TAB = LDS_A2 + K3 * CB * FB;
+  static constexpr int LDS_BYTES = LDS_TAB + C::tab_bytes(GT);
   static_assert(LDS_BYTES <= 160 * 1024, "LDS budget");
   // FP32: layer-2 k-steps in flight (one block of 4,096 cells: six 20.7 us, eight
   // 19.4, ten 19.7, twelve spill and take 21.7; two blocks are bound by products)
@@ -184,6 +187,8 @@ __global__ __launch_bounds__(S::NW * 64, 2) void small_step_kernel(StepArgs a) {
   for (int i = threadIdx.x; i < DConst::N; i += NT) dcl[i] = a.dc[i];
   for (int i = threadIdx.x; i < FConst::N; i += NT) fcl[i] = a.fc[i];
   for (int i = threadIdx.x; i < NQ1 * CB * FB / 16; i += NT) ((i4 *)A0)[i] = i4{0, 0, 0, 0};
+  for (int i = threadIdx.x; i < C::tab_bytes(S::GT) / 16; i += NT)
+    ((i4 *)(smem + S::LDS_TAB))[i] = ((const i4 *)a.gtab)[i];
   if constexpr (RPQ > 1) {
     for (int i = threadIdx.x; i < CB * FB / 16; i += NT) {
       ((i4 *)(A1 + (K2 - 1) * CB * FB))[i] = i4{0, 0, 0, 0};
@@ -262,6 +267,20 @@ __global__ __launch_bounds__(S::NW * 64, 2) void small_step_kernel(StepArgs a) {
       for (int u = 0; u < N(); ++u) z(u) = Op::mma(wf(u), x(u), z(u));
     }
   };
+  // hidden activation of the first n blocks
+  auto act = [&](auto &z, int n) {
+    if constexpr (S::GT == 0) {
+      gelu_stages(z, n);
+    } else {
+#pragma unroll
+      for (int u = 0; u < (int)(sizeof(z) / sizeof(f4)); ++u)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (u < n)
+            z[u][r] = S::GT == 1 ? gelu_tab(z[u][r], (const f4 *)(smem + S::LDS_TAB))
+                                 : gelu_tab16(z[u][r], (const h4v *)(smem + S::LDS_TAB));
+    }
+  };
   // a row-block's starting accumulators, scaled result, and store of layer l's
   // activations y as the next layer's input
   auto init = [&](const float *B, int rb) {
@@ -329,7 +348,7 @@ __global__ __launch_bounds__(S::NW * 64, 2) void small_step_kernel(StepArgs a) {
         }
 #pragma unroll
         for (int u = 0; u < N; ++u) scale(z[u], 0, B1, u < G * CB ? 3 * w + k0 + u / CB : 24);
-        gelu_stages<N>(z, N);
+        act(z, N);
 #pragma unroll
         for (int u = 0; u < N; ++u)
           if (u < G * CB) put(z[u], 0, 3 * w + k0 + u / CB, u % CB, A1);
@@ -385,15 +404,15 @@ __global__ __launch_bounds__(S::NW * 64, 2) void small_step_kernel(StepArgs a) {
       else run(integral_constant<int, 0>{});
 #pragma unroll
       for (int c = 0; c < CB; ++c) scale(z0[c], 1, B2, w), scale(z1[c], 1, B2, rb2b);
-      gelu_stages<CB>(z0, CB);
+      act(z0, CB);
 #pragma unroll
       for (int c = 0; c < CB; ++c) put(z0[c], 1, w, c, A2);
       if (low) {
-        gelu_stages<CB>(z1, CB);
+        act(z1, CB);
 #pragma unroll
         for (int c = 0; c < CB; ++c) put(z1[c], 1, rb2b, c, A2);
       } else if (pre) {
-        gelu_stages<CB>(z1, 1);
+        act(z1, 1);
         put(z1[0], 1, rb2b, uc, A2);
       }
     }
@@ -414,7 +433,7 @@ __global__ __launch_bounds__(S::NW * 64, 2) void small_step_kernel(StepArgs a) {
         }
 #pragma unroll
         for (int c = 0; c < CB; ++c) scale(z[c], 2, B3, w);
-        gelu_stages<CB>(z, CB);
+        act(z, CB);
 #pragma unroll
         for (int c = 0; c < CB; ++c) put(z[c], 2, w, c, A3);
       } else if (RPQ > 1) {
@@ -472,27 +491,31 @@ template <class S> static hipError_t launch_small(const StepArgs &a0, int n_cu, 
 // MAXCB (four; two in FP32, whose four blocks do not fit the LDS).  A tile of one
 // / two / four blocks takes 4.0 / 5.8 / 8.9 us in BF16, 4.1 / 5.3 / 8.5 in FP8,
 // 13.8 / 20.8 in FP32, so the fewest rounds are the fastest.
-template <class C, int MAXCB> static hipError_t small_step(const StepArgs &a, int n_cu, hipStream_t s) {
+template <class C, int MAXCB, int GT> static hipError_t small_step(const StepArgs &a, int n_cu, hipStream_t s) {
   const int64_t blocks = (a.n + 15) / 16;
-  if (blocks <= n_cu) return launch_small<Small<C, 1>>(a, n_cu, s);
-  if (MAXCB == 2 || blocks <= 2 * n_cu) return launch_small<Small<C, 2>>(a, n_cu, s);
-  return launch_small<Small<C, MAXCB>>(a, n_cu, s);
+  if (blocks <= n_cu) return launch_small<Small<C, 1, GT>>(a, n_cu, s);
+  if (MAXCB == 2 || blocks <= 2 * n_cu) return launch_small<Small<C, 2, GT>>(a, n_cu, s);
+  return launch_small<Small<C, MAXCB, GT>>(a, n_cu, s);
 }
 
 template <class S> static hipError_t small_lds() {
   return hipFuncSetAttribute((const void *)small_step_kernel<S>, hipFuncAttributeMaxDynamicSharedMemorySize,
                              S::LDS_BYTES);
 }
-template <class C, int MAXCB> static hipError_t small_prepare() {
-  hipError_t e = small_lds<Small<C, 1>>();
-  if (e == hipSuccess) e = small_lds<Small<C, 2>>();
-  if (e == hipSuccess && MAXCB > 2) e = small_lds<Small<C, MAXCB>>();
+template <class C, int MAXCB, int GT> static hipError_t small_prepare() {
+  hipError_t e = small_lds<Small<C, 1, GT>>();
+  if (e == hipSuccess) e = small_lds<Small<C, 2, GT>>();
+  if (e == hipSuccess && MAXCB > 2) e = small_lds<Small<C, MAXCB, GT>>();
   return e;
 }
 template <class C, bool WITH_CALIB, int MAXCB> static void fill_small_layout(NetLayout *L) {
   fill_layout<C, WITH_CALIB>(L);
-  L->pick = small_step<C, MAXCB>;
-  L->pick_prepare = small_prepare<C, MAXCB>;
+  L->pick[0] = small_step<C, MAXCB, 0>;
+  L->pick[1] = small_step<C, MAXCB, 1>;
+  L->pick[2] = small_step<C, MAXCB, 2>;
+  L->pick_prepare[0] = small_prepare<C, MAXCB, 0>;
+  L->pick_prepare[1] = small_prepare<C, MAXCB, 1>;
+  L->pick_prepare[2] = small_prepare<C, MAXCB, 2>;
   L->pick_species = 18;                              // its slots
 }
 

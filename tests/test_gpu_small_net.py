@@ -56,3 +56,20 @@ def test_species_counts(S):
         ref = chem.step(st.T, st.P, st.Y, net, thermo=thermo)
         assert rel_err(Yn.cpu().numpy()[:, :n], ref["Y_new"]) <= 1e-5
         assert rel_err(Tn.cpu().numpy(), ref["T_new"], floor=1.0) <= 1e-5
+
+
+@pytest.mark.parametrize("prec,gelu", [("fp32", "table"), ("bf16", "table16"), ("fp8", "table")])
+def test_tables_give_the_same_bits_at_every_size(prec, gelu):
+    """The tabulated GELU in the same kernel (its values against the oracle:
+    test_gpu_step.py)."""
+    net = synth.make_net(1, bias_scale=0.1, out_stats=True)
+    h = make_handle(net, prec, gelu=gelu, act_amax=np.array([6.0, 4.0, 4.0, 4.0]) if prec == "fp8" else None)
+    T, P, Y = dev_state(synth.make_state(1, BIG))
+    Yb, _ = h.step(T, P, Y)
+    torch.cuda.synchronize()
+    o = 77
+    for n in (1, 17, 4096, 4097, 8193):
+        print(f"case small net {gelu} {prec} n={n}", flush=True)
+        Yn, _ = h.step(T[o:o + n].contiguous(), P[o:o + n].contiguous(), Y[:, o:o + n].contiguous())
+        torch.cuda.synchronize()
+        assert torch.equal(Yn, Yb[:, o:o + n]), n
