@@ -925,16 +925,17 @@ int64_t params_of(const int *w) {
   return o;
 }
 
-// 32-sample blocks per weight-gradient split of nk blocks: at most 52 splits of
-// the second layer (with its three tiles and the other layers' fewer, longer
-// splits, one round of workgroups on 256 CUs), 24 for batches of up to 288
-// blocks, whose partial sums (0.42 MB a split) would outgrow the rest of the
-// scratch; at least two blocks.
+// Splits of the weight gradients' batch of nk 32-sample blocks: at most 34 of
+// the second and third layer (with their tiles and the other layers' fewer,
+// longer splits, one round of workgroups on 256 CUs); 27 for 129 to 288 blocks,
+// whose partial sums (0.43 MB a split) would outgrow the static scratch of the
+// allocation-free step.  64 / 4,096 / 8,192 samples a step: 24
+// splits of two blocks at least 47.2 / 58.9 / 74.6 us, so 45.0 / 56.5 / 72.7.
+int64_t max_splits(int64_t nk) { return nk <= 128 ? 34 : nk <= 288 ? 27 : 34; }
 int split_blocks(int64_t nk) {
-  const int64_t most = nk <= 288 ? 24 : 34, k = (nk + most - 1) / most;
-  return (int)(k < 2 ? 2 : k);
+  const int64_t most = max_splits(nk), k = (nk + most - 1) / most;
+  return (int)(k < 1 ? 1 : k);
 }
-int64_t max_splits(int64_t nk) { return nk <= 288 ? 24 : 34; }
 
 // Tiles of 16 samples while they fit one round of workgroups (the chain of a
 // tile's eight products takes 18 us with 16 samples and 29 with 32), of 32
