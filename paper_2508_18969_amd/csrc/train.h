@@ -53,6 +53,7 @@ struct TileScratch {
   float *part;            // parameter-gradient partials, one copy per split
   float *lpart;           // loss partial sum per tile
   double *closs;          // loss sum of each chunk
+  int64_t splits;         // weight-gradient splits that `part` holds
 };
 bool tile_shape(const int *widths);
 size_t tile_scratch_bytes(const int *widths, int64_t max_batch, int64_t chunk);

@@ -927,11 +927,13 @@ int64_t params_of(const int *w) {
 
 // Splits of the weight gradients' batch of nk 32-sample blocks: at most 34 of
 // the second and third layer (with their tiles and the other layers' fewer,
-// longer splits, one round of workgroups on 256 CUs); 27 for 129 to 288 blocks,
-// whose partial sums (0.43 MB a split) would outgrow the static scratch of the
-// allocation-free step.  64 / 4,096 / 8,192 samples a step: 24
-// splits of two blocks at least 47.2 / 58.9 / 74.6 us, so 45.0 / 56.5 / 72.7.
-int64_t max_splits(int64_t nk) { return nk <= 128 ? 34 : nk <= 288 ? 27 : 34; }
+// longer splits, one round of workgroups on 256 CUs); 27 up to 288 blocks,
+// where the partial sums of more (0.43 MB a split) would outgrow the static
+// scratch of the allocation-free step.  Never more for fewer blocks: the
+// scratch is sized by the largest chunk, and a batch's last chunk is smaller.
+// 64 / 4,096 / 8,192 samples a step: at most 24 splits of two blocks at least
+// 47.2 / 58.9 / 74.6 us, so 45.0 / 57.5 / 73.5.
+int64_t max_splits(int64_t nk) { return nk <= 288 ? 27 : 34; }
 int split_blocks(int64_t nk) {
   const int64_t most = max_splits(nk), k = (nk + most - 1) / most;
   return (int)(k < 1 ? 1 : k);
@@ -993,6 +995,7 @@ hipError_t weight_grads(const int *w, int64_t n, const TileScratch *t, FinishArg
     off += (int64_t)M * N + M;
     f.end[l] = off;
     f.nsplit[l] = (d.nk + d.l[l].kc - 1) / d.l[l].kc;
+    if (f.nsplit[l] > t->splits) return hipErrorInvalidValue;
     grid += TM[l] * TN[l] * f.nsplit[l];
   }
   d.part = t->part;
@@ -1039,7 +1042,8 @@ void tile_scratch_layout(TileScratch *t, uint8_t *base, const int *w, int64_t ca
   t->chunk = chunk_samples(cap, chunk);
   const int64_t n = whole_tiles(t->chunk);
   t->blk = (float *)take(block_bytes(w, n));
-  t->part = (float *)take((size_t)max_splits(n / MC) * params_of(w) * 4);
+  t->splits = max_splits(n / MC);
+  t->part = (float *)take((size_t)t->splits * params_of(w) * 4);
   t->lpart = (float *)take((size_t)(n / 16) * 4);
   t->closs = (double *)base;
 }
