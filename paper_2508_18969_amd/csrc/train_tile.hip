@@ -309,22 +309,27 @@ __global__ __launch_bounds__(NW * 64, 1) void tile_kernel(TileArgs a) {
 #pragma unroll
       for (int k = 0; k < 3; ++k) *(u2 *)(p + k * FB + 8) = u2{0u, 0u};
   };
-  // rows of row-block rb (of H rows, the first at row r0) of cell-block c, in
-  // the caller's array dst of leading dimension a.ld, or (NULL) in the tile's
-  // scratch block: a resource at the block's first element, one per-lane offset
+  // rows of row-block rb (of H rows, the first at row r0) from column col on, in
+  // the tile's scratch block: a resource at the block's first element, one
+  // per-lane offset
   float *blk = a.blk;
   auto block_of = [&](int64_t t) { return a.blk + t * TS / MC * rows(a.D, a.S) * MC + t * TS % MC; };
-  auto store = [&](float *dst, int r0, int rb, int H, int64_t col, bool ok, f4 v) {
-    const int64_t ld = dst ? a.ld : MC;
-    const rsrc_t o = __builtin_amdgcn_make_buffer_rsrc((dst ? dst : blk) + (r0 + 16 * rb) * ld + col,
-                                                       (short)0, -1, 0x00020000);
-    const int vo = (int)((uint32_t)(4 * g) * (uint32_t)ld + (uint32_t)cl) * 4;
-    const int so = (int)((uint32_t)ld * 4u);
-    if (!ok) return;
+  auto store = [&](int r0, int rb, int H, int col, f4 v) {
+    const rsrc_t o = __builtin_amdgcn_make_buffer_rsrc(blk + (r0 + 16 * rb) * MC + col, (short)0, -1, 0x00020000);
+    const int vo = (4 * g * MC + cl) * 4;
 #pragma unroll
     for (int r = 0; r < 4; ++r)
       if (16 * rb + 15 < H || 16 * rb + 4 * g + r < H)
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, (float)v[r]), o, vo, r * so, 0);
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, (float)v[r]), o, vo, r * MC * 4, 0);
+  };
+  // the same rows of one of the caller's arrays (leading dimension a.ld): 64-bit
+  // addresses, since sixteen rows pass 4 GiB from ld = 71.6 million on
+  auto store_to = [&](float *dst, int r0, int rb, int H, int64_t col, bool ok, f4 v) {
+    float *const p = dst + (int64_t)(r0 + 16 * rb + 4 * g) * a.ld + (col + cl);
+    if (!ok) return;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (16 * rb + 15 < H || 16 * rb + 4 * g + r < H) p[r * a.ld] = v[r];
   };
 
   // Wave w owns the row-blocks v = w, w + 8, ...  The input of a tile is made
@@ -370,7 +375,7 @@ __global__ __launch_bounds__(NW * 64, 1) void tile_kernel(TileArgs a) {
     if constexpr (FWD) put(smem + L::X, XH, 2, XC, y);
     if constexpr (BWD) {
       blk = block_of(t);
-      store(nullptr, 0, XH, a.D, 16 * XC, true, y);
+      store(0, XH, a.D, 16 * XC, y);
     }
   };
   if (XW && FWD) {
@@ -395,9 +400,9 @@ __global__ __launch_bounds__(NW * 64, 1) void tile_kernel(TileArgs a) {
       }
       if constexpr (FWD) put(dst, rb, R, c, y);
       if constexpr (MODE == TILE_FWD) {
-        if (a.zs) store(a.zs, r0, rb, H, s0 + 16 * c, cell < a.B, z);
+        if (a.zs) store_to(a.zs, r0, rb, H, s0 + 16 * c, cell < a.B, z);
       } else {
-        store(nullptr, row_a(a.D) + r0, rb, H, 16 * c, true, y);
+        store(row_a(a.D) + r0, rb, H, 16 * c, y);
       }
     };
     f4 g1[4][CB], g2[2][CB], g3[CB];
@@ -480,19 +485,20 @@ __global__ __launch_bounds__(NW * 64, 1) void tile_kernel(TileArgs a) {
     } else {
       // ---------------------------------------------------------- saved z
       load_target();
+      // (64-bit addresses, as in store_to; rows and samples past the batch read
+      // the last row, the first sample)
       auto load_z = [&](int r0, int rb, int H, int c) {
-        const rsrc_t zr = __builtin_amdgcn_make_buffer_rsrc((void *)(a.z + (r0 + 16 * rb) * a.ld + (s0 < a.B ? s0 : 0)),
-                                                            (short)0, -1, 0x00020000);
         const bool ok = s0 + 16 * c + cl < a.B;
+        const float *const p = a.z + (ok ? s0 + 16 * c + cl : 0);
+        const int go = opaque_v(g);
         f4 z;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          // (rows and samples past the batch: the first one's, zeroed)
-          const bool in = ok && (16 * rb + 15 < H || 16 * rb + 4 * g + r < H);
-          const uint32_t o = in ? (uint32_t)(4 * g + r) * (uint32_t)a.ld + (uint32_t)(16 * c + cl) : 0u;
-          const float x = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(zr, (int)(o * 4u), 0, 0));
-          z[r] = in ? x : 0.0f;
+          const int row = 16 * rb + 4 * go + r;
+          z[r] = p[(int64_t)(r0 + (16 * rb + 15 < H || row < H ? row : H - 1)) * a.ld];
+          if (!ok || !(16 * rb + 15 < H || row < H)) z[r] = 0.0f;
         }
+        __builtin_amdgcn_sched_barrier(0);
         return z;
       };
 #pragma unroll
@@ -536,7 +542,7 @@ __global__ __launch_bounds__(NW * 64, 1) void tile_kernel(TileArgs a) {
         w4.template run<CB, 1>(wr, voff, Cq, ocb, lane, o);
       }
       if constexpr (MODE == TILE_FWD) {
-        store(a.out, 0, orb, a.S, s0 + 16 * ocb, ocell < a.B, o[0][0]);
+        store_to(a.out, 0, orb, a.S, s0 + 16 * ocb, ocell < a.B, o[0][0]);
       } else {
         f4 d = tgt;
         if constexpr (MODE == TILE_TRAIN) {
@@ -553,7 +559,7 @@ __global__ __launch_bounds__(NW * 64, 1) void tile_kernel(TileArgs a) {
           if (lane == 0) red[w] = s;
         }
         put(smem + L::DO, orb, 2, ocb, d);
-        store(nullptr, row_do(a.D), orb, a.S, 16 * ocb, true, d);
+        store(row_do(a.D), orb, a.S, 16 * ocb, d);
       }
     }
     if constexpr (FWD)
@@ -581,7 +587,7 @@ __global__ __launch_bounds__(NW * 64, 1) void tile_kernel(TileArgs a) {
       for (int c = 0; c < CB; ++c) {
         const f4 d = acc[0][c] * g3[c];
         put(smem + L::D3, v, R3, c, d);
-        store(nullptr, row_dz(a.D) + H1 + H2, v, H3, 16 * c, true, d);
+        store(row_dz(a.D) + H1 + H2, v, H3, 16 * c, d);
       }
     }
     // ------------------------------------------------------------ dZ_2
@@ -602,7 +608,7 @@ __global__ __launch_bounds__(NW * 64, 1) void tile_kernel(TileArgs a) {
         for (int c = 0; c < CB; ++c) {
           const f4 d = acc[i][c] * g2[i][c];
           put(smem + L::D2, v + NW * i, R2, c, d);
-          store(nullptr, row_dz(a.D) + H1, v + NW * i, H2, 16 * c, true, d);
+          store(row_dz(a.D) + H1, v + NW * i, H2, 16 * c, d);
         }
     };
     if (v + NW < R2) dz2(std::integral_constant<int, 2>{});
@@ -621,7 +627,7 @@ __global__ __launch_bounds__(NW * 64, 1) void tile_kernel(TileArgs a) {
 #pragma unroll
         for (int c = 0; c < CB; ++c) {
           const f4 d = acc[i][c] * (ps == 0 ? g1[i][c] : g1[2 + i][c]);
-          store(nullptr, row_dz(a.D), v + NW * (2 * ps + i), H1, 16 * c, true, d);
+          store(row_dz(a.D), v + NW * (2 * ps + i), H1, 16 * c, d);
           // (the input gradient's operand, in the place of the derivative)
           if constexpr (GX) (ps == 0 ? g1[i][c] : g1[2 + i][c]) = d;
         }
@@ -655,7 +661,7 @@ __global__ __launch_bounds__(NW * 64, 1) void tile_kernel(TileArgs a) {
         s.start(wr, voff, T1, orb);
         f4 acc[1][1] = {{zero}};
         s.template run<CB, 1>(wr, voff, A, ocb, lane, acc);
-        store(a.gx, 0, orb, a.D, s0 + 16 * ocb, ocell < a.B, acc[0][0]);
+        store_to(a.gx, 0, orb, a.D, s0 + 16 * ocb, ocell < a.B, acc[0][0]);
       }
       lds_barrier();      // (A is written again)
     }
