@@ -348,7 +348,9 @@ __global__ __launch_bounds__(T::NT, 1) void layer_kernel(LayerArgs a) {
 // (6.4), 16 x 1600 4.3 (3.7).
 //
 // FUSED: the features are rounded as in the fused kernel (T, P and the species
-// of their slots through FP32), for its networks' small batches.
+// of their slots through FP32), for its networks' small batches.  The property
+// networks' inputs are rounded once, FP64 to the operand format, on both paths
+// (in the fused kernel the compiler folds the two conversions).
 constexpr int FWCB = 2;
 template <class Op, bool PROP, bool FUSED, bool DBG = false>
 __global__ __launch_bounds__(256) void first_kernel(FirstArgs a) {
