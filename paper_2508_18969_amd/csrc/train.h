@@ -52,7 +52,7 @@ struct TileScratch {
   float *blk;             // per tile of 32 samples: input, activations and gradients
   float *part;            // parameter-gradient partials, one copy per split
   float *lpart;           // loss partial sum per tile
-  double *closs;          // loss sum of each chunk
+  double *closs;          // loss sum of the chunks so far
   int64_t splits;         // weight-gradient splits that `part` holds
 };
 bool tile_shape(const int *widths);

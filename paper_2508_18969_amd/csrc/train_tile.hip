@@ -851,9 +851,9 @@ struct FinishArgs {
   float *grads;
   float *p, *m, *v;        // Adam update, or p = NULL
   float lr, c1, c2;
-  const float *lpart;      // loss: nl partial sums of this chunk (the chunk-th), or NULL
-  int64_t nl, chunk;
-  double *closs;           // sums of the chunks
+  const float *lpart;      // loss: nl partial sums of this chunk, or NULL
+  int64_t nl;
+  double *closs;           // sum of the chunks so far
   double denom;
   float *loss;             // after the last chunk, else NULL
 };
@@ -878,16 +878,15 @@ __global__ __launch_bounds__(256) void finish_kernel(FinishArgs a) {
 #pragma unroll
       for (int u = 0; u < 8; ++u) s += (double)v[u];
     }
-    if (a.loss)
-      for (int64_t i = threadIdx.x; i < a.chunk; i += 256) s += a.closs[i];
 #pragma unroll
     for (int k = 32; k >= 1; k >>= 1) s += __shfl_xor(s, k);
     if (l == 0) qs[w] = s;
     __syncthreads();
     if (threadIdx.x == 0) {
       s = ((qs[0] + qs[1]) + qs[2]) + qs[3];
+      if (a.accum) s += *a.closs;
       if (a.loss) *a.loss = (float)(s / a.denom);
-      else a.closs[a.chunk] = s;
+      else *a.closs = s;
     }
     return;
   }
@@ -933,13 +932,17 @@ int64_t params_of(const int *w) {
 
 // Splits of the weight gradients' batch of nk 32-sample blocks: at most 34 of
 // the second and third layer (with their tiles and the other layers' fewer,
-// longer splits, one round of workgroups on 256 CUs); 27 up to 288 blocks,
-// where the partial sums of more (0.43 MB a split) would outgrow the static
-// scratch of the allocation-free step.  Never more for fewer blocks: the
-// scratch is sized by the largest chunk, and a batch's last chunk is smaller.
-// 64 / 4,096 / 8,192 samples a step: at most 24 splits of two blocks at least
-// 47.2 / 58.9 / 74.6 us, so 45.0 / 57.5 / 73.5.
-int64_t max_splits(int64_t nk) { return nk <= 288 ? 27 : 34; }
+// longer splits, one round of workgroups on 256 CUs), one block at least; 27 up
+// to 293 blocks, where the partial sums of more (0.43 MB a split) would outgrow
+// the static scratch of the allocation-free step (293 blocks, 9,376 samples: the
+// largest chunk of one species that it takes; 9,184 of 17).  Never more for
+// fewer blocks: the scratch is sized by the largest chunk, and a batch's last
+// chunk is smaller.  64 / 4,096 / 8,192 samples a step: at most 24 splits of two
+// blocks at least 47.2 / 58.9 / 74.6 us, so 45.0 / 57.5 / 73.5.
+int64_t max_splits(int64_t nk) {
+  const int64_t most = nk <= 293 ? 27 : 34;
+  return nk < most ? nk : most;
+}
 int split_blocks(int64_t nk) {
   const int64_t most = max_splits(nk), k = (nk + most - 1) / most;
   return (int)(k < 1 ? 1 : k);
@@ -1032,7 +1035,7 @@ size_t tile_scratch_bytes(const int *w, int64_t cap, int64_t chunk) {
   if (cap <= 0) return b;
   const int64_t c = chunk_samples(cap, chunk), n = whole_tiles(c);
   return b + block_bytes(w, n) + up256((size_t)max_splits(n / MC) * params_of(w) * 4) +
-         up256((size_t)(n / 16) * 4) + up256((size_t)((cap + c - 1) / c) * 8);
+         up256((size_t)(n / 16) * 4) + up256(sizeof(double));
 }
 
 void tile_scratch_layout(TileScratch *t, uint8_t *base, const int *w, int64_t cap, int64_t chunk) {
@@ -1128,8 +1131,7 @@ hipError_t tile_train_step(const int *w, int64_t B, int64_t ld, const double *T,
   if (B > t->cap) return hipErrorInvalidValue;
   hipError_t e = pack(w, params, t->pack, s);
   const double denom = (double)B * w[4];
-  int64_t k = 0;
-  for (int64_t c0 = 0; c0 < B && e == hipSuccess; c0 += t->chunk, ++k) {
+  for (int64_t c0 = 0; c0 < B && e == hipSuccess; c0 += t->chunk) {
     const int64_t n = B - c0 < t->chunk ? B - c0 : t->chunk;
     TileArgs a{};
     a.T = T + c0;
@@ -1154,7 +1156,6 @@ hipError_t tile_train_step(const int *w, int64_t B, int64_t ld, const double *T,
     f.grads = grads;
     f.lpart = t->lpart;
     f.nl = tiles_of(n, tile_samples(n, n_cu));
-    f.chunk = k;
     f.closs = t->closs;
     if (c0 + n >= B) {
       f.p = params;
