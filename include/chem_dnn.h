@@ -249,8 +249,9 @@ int32_t chem_dnn_destroy(chem_dnn *h);
  * layer against an exact recomputation from the very operands the matrix
  * cores received, and each activation against its accumulators).  Runs the
  * network of chem_dnn_step on n <= CHEM_DNN_DEBUG_MAX_CELLS cells with the
- * same kernels, operand formats and schedules, and instead of the update
- * writes, for every layer l = 0 .. L-1:
+ * kernels, operand formats and schedules that chem_dnn_step takes for a batch
+ * of n cells (larger batches may take others, with the same results), and
+ * instead of the update writes, for every layer l = 0 .. L-1:
  *   qin  device FP32 [sum_l widths[l]][n]; rows in_row(l) = sum_{k<l} widths[k]
  *        onward: layer l's input as the operand values fed to the matrix
  *        cores (quantised to the handle's precision; for FP8 the scaled

@@ -345,17 +345,25 @@ StepArgs step_args(chem_dnn *h, int64_t n, int64_t ld, const double *T, const do
 // biases, row-blocks and input k-steps per layer, activation buffers.
 struct LayerNet {
   int fmt, L, n_cu;      // fmt: 0 FP32, 1 BF16, 2 FP16 operands
-  const int *R, *NQ;
+  const int *widths, *R, *NQ;
   void *const *w;
   float *const *b;
   uint8_t *const *act;
 };
 
+// Layer dump of some cells: operand values and accumulators, rows of all
+// layers one after the other, leading dimension ld.
+struct Dump {
+  float *qin, *acc;
+  int64_t ld;
+};
+
 // One chunk: the first layer with the input transform, one launch per further
 // hidden layer, the output layer with the post-processing.  `fa` and `ea`
-// hold the fields; the rest is filled in here.
+// hold the fields; the rest is filled in here.  With a dump, the kernels' debug
+// builds, without the post-processing.
 hipError_t run_layers(const LayerNet &n, FirstArgs fa, LastArgs ea, int nc, bool prop, bool fused,
-                      hipStream_t s) {
+                      hipStream_t s, const Dump *dump = nullptr) {
   const int ncb = (nc + 15) / 16, L = n.L, ks = ks_of(n.fmt);
   fa.nc = nc;
   fa.NCB = ncb;
@@ -365,13 +373,51 @@ hipError_t run_layers(const LayerNet &n, FirstArgs fa, LastArgs ea, int nc, bool
   fa.R = n.R[0];
   fa.RO = n.NQ[1] * ks / 16;
   fa.n_cu = n.n_cu;
-  hipError_t e = launch_first(n.fmt, fa, prop, fused, false, s);
+  float *qin = nullptr, *acc = nullptr;    // (dump: of the next layer)
+  if (dump) {
+    fa.dbg_in = dump->qin;
+    fa.dbg_acc = dump->acc;
+    fa.dbg_rows = n.widths[1];
+    fa.dbg_ld = dump->ld;
+    qin = dump->qin + n.widths[0] * dump->ld;
+    acc = dump->acc + n.widths[1] * dump->ld;
+  }
+  hipError_t e = launch_first(n.fmt, fa, prop, fused, dump != nullptr, s);
   int cur = 0;
+  // the operands of layer l, from the activation buffer it reads
+  auto dump_input = [&](int l) {
+    if (!dump || e != hipSuccess) return;
+    e = launch_frag_decode(n.fmt, n.act[cur], ncb, n.widths[l], nc, qin, dump->ld, s);
+    qin += n.widths[l] * dump->ld;
+  };
   for (int l = 1; l < L - 1 && e == hipSuccess; ++l) {
-    LayerArgs la{(const uint8_t *)n.w[l], n.b[l], n.act[cur], n.act[cur ^ 1], n.R[l], n.NQ[l], ncb,
-                 n.NQ[l + 1] * ks / 16, n.n_cu, nullptr, 0, 0};
-    e = launch_layer(n.fmt, la, s);
+    LayerArgs la{};
+    la.W = (const uint8_t *)n.w[l];
+    la.bias = n.b[l];
+    la.X = n.act[cur];
+    la.Y = n.act[cur ^ 1];
+    la.R = n.R[l];
+    la.NQ = n.NQ[l];
+    la.NCB = ncb;
+    la.RO = n.NQ[l + 1] * ks / 16;
+    la.n_cu = n.n_cu;
+    if (dump) {
+      dump_input(l);
+      la.dbg_acc = acc;
+      la.dbg_rows = n.widths[l + 1];
+      la.dbg_n = nc;
+      la.dbg_ld = dump->ld;
+      acc += n.widths[l + 1] * dump->ld;
+      if (e == hipSuccess) e = launch_layer_dbg(n.fmt, la, s);
+    } else {
+      e = launch_layer(n.fmt, la, s);
+    }
     cur ^= 1;
+  }
+  if (dump) {
+    dump_input(L - 1);
+    ea.dbg_acc = acc;
+    ea.dbg_ld = dump->ld;
   }
   ea.nc = nc;
   ea.NCB = ncb;
@@ -379,14 +425,15 @@ hipError_t run_layers(const LayerNet &n, FirstArgs fa, LastArgs ea, int nc, bool
   ea.bias = n.b[L - 1];
   ea.X = n.act[cur];
   ea.NQ = n.NQ[L - 1];
-  return e == hipSuccess ? launch_last(n.fmt, ea, prop, false, s) : e;
+  return e == hipSuccess ? launch_last(n.fmt, ea, prop, dump != nullptr, s) : e;
 }
 
 // Cells [n0, n0 + nc) of a chemistry update, layer by layer.
 hipError_t run_chem_layers(chem_dnn *h, int64_t n0, int nc, int64_t ld, const double *T,
                            const double *P, const double *Y, double *Y_out, double *T_out,
-                           double *omega, double inv_dt, uint32_t *n_bad, hipStream_t s) {
-  const LayerNet net{h->prec, h->L, h->n_cu, h->lR, h->lNQ, h->wpack, h->bias, h->act};
+                           double *omega, double inv_dt, uint32_t *n_bad, hipStream_t s,
+                           const Dump *dump = nullptr) {
+  const LayerNet net{h->prec, h->L, h->n_cu, h->widths, h->lR, h->lNQ, h->wpack, h->bias, h->act};
   FirstArgs fa{};
   fa.T = T;
   fa.P = P;
@@ -411,7 +458,7 @@ hipError_t run_chem_layers(chem_dnn *h, int64_t n0, int nc, int64_t ld, const do
   ea.dc = h->dc;
   ea.inv_dt = inv_dt;
   ea.thermo = h->thermo;
-  return run_layers(net, fa, ea, nc, false, !h->layered, s);
+  return run_layers(net, fa, ea, nc, false, !h->layered, s, dump);
 }
 
 // The layer-by-layer path over chunks of kChunk cells.
@@ -562,19 +609,24 @@ int64_t chain_rest(int64_t n, int64_t round, int64_t limit, int prec) {
 }
 
 // The fused kernel over whole rounds of its tiles, the layer-by-layer kernels
-// over the rest of the batch where that is small.
-int32_t run_fused(chem_dnn *h, StepArgs a, hipStream_t s) {
-  const auto pick = h->S <= h->lay.pick_species ? h->lay.pick[h->gelu_form] : nullptr;
+// over the rest of the batch where that is small.  With a dump (tanh GELU), the
+// debug builds of the same kernels.
+int32_t run_fused(chem_dnn *h, StepArgs a, hipStream_t s, const Dump *dump = nullptr) {
+  const bool small = h->S <= h->lay.pick_species;
+  const auto pick = !small ? nullptr : dump ? h->lay.pick_dbg : h->lay.pick[h->gelu_form];
   const int64_t nc = chain_rest(a.n, (int64_t)h->n_cu * h->lay.MC, h->chain, h->prec), n = a.n - nc;
   hipError_t e = hipSuccess;
   if (n > 0) {
     a.n = n;
     a.ntiles = (n + h->lay.MC - 1) / h->lay.MC;
-    e = pick ? pick(a, h->n_cu, s) : step_launch(h)(a, grid_for(h, a.ntiles), s);
+    e = pick ? pick(a, h->n_cu, s) : (dump ? h->lay.dbg : step_launch(h))(a, grid_for(h, a.ntiles), s);
   }
-  if (nc && e == hipSuccess)
+  if (nc && e == hipSuccess) {
+    Dump rest{};
+    if (dump) rest = {dump->qin + n, dump->acc + n, dump->ld};
     e = run_chem_layers(h, n, (int)nc, a.ld, a.T, a.P, a.Y, a.Y_out, a.T_out, a.omega, a.inv_dt,
-                        a.n_bad, s);
+                        a.n_bad, s, dump ? &rest : nullptr);
+  }
   return hip_status(e);
 }
 
@@ -921,49 +973,22 @@ int32_t chem_dnn_debug_layers(chem_dnn *h, int64_t n, int64_t ld, const double *
   if (!T || !P || !Y || !qin || !acc) return CHEM_DNN_EINVAL;
   if (h->gelu_form != CHEM_DNN_GELU_TANH) return CHEM_DNN_EUNSUPPORTED;
   hipStream_t s = (hipStream_t)stream;
-  int in_row[8], acc_row[8];
-  for (int l = 0, ri = 0, ra = 0; l < h->L; ++l) {
-    in_row[l] = ri;
-    acc_row[l] = ra;
+  const Dump dump{qin, acc, n};
+  if (h->layered)      // (one chunk: n <= CHEM_DNN_DEBUG_MAX_CELLS < kChunk)
+    return hip_status(run_chem_layers(h, 0, (int)n, ld, T, P, Y, nullptr, nullptr, nullptr, 0.0, nullptr, s,
+                                      &dump));
+  if (h->lay.pick_dbg && h->lay.pick_dbg_prepare() != hipSuccess) return CHEM_DNN_EHIP;
+  StepArgs a = step_args(h, n, ld, T, P, Y, nullptr, nullptr, nullptr);
+  a.dbg_in = qin;
+  a.dbg_acc = acc;
+  a.dbg_ld = n;
+  for (int l = 0, ri = 0, ra = 0; l < 4; ++l) {
+    a.dbg_in_row[l] = ri;
+    a.dbg_acc_row[l] = ra;
     ri += h->widths[l];
     ra += h->widths[l + 1];
   }
-  if (!h->layered) {
-    if (!h->lay.dbg) return CHEM_DNN_EUNSUPPORTED;
-    StepArgs a = step_args(h, n, ld, T, P, Y, nullptr, nullptr, nullptr);
-    a.dbg_in = qin;
-    a.dbg_acc = acc;
-    for (int l = 0; l < 4; ++l) {
-      a.dbg_in_row[l] = in_row[l];
-      a.dbg_acc_row[l] = acc_row[l];
-    }
-    return hip_status(h->lay.dbg(a, grid_for(h, a.ntiles), s));
-  }
-  // layer by layer: one chunk (n <= CHEM_DNN_DEBUG_MAX_CELLS < kChunk)
-  const int fmt = h->prec, L = h->L;
-  const int nc = (int)n, ncb = (nc + 15) / 16;
-  FirstArgs fa{T, P, Y, ld, 0, nc, ncb, h->D, (const uint8_t *)h->wpack[0], h->bias[0], h->act[0],
-               h->lR[0], h->lR[0], h->fc, h->dc, h->n_cu, 0, qin, acc, h->widths[1]};
-  hipError_t e = launch_first(fmt, fa, false, false, true, s);
-  int cur = 0;
-  for (int l = 1; l < L && e == hipSuccess; ++l) {
-    // layer l's input, then the layer
-    e = launch_frag_decode(fmt, h->act[cur], ncb, h->widths[l], nc, qin + (size_t)in_row[l] * nc, s);
-    if (e != hipSuccess) break;
-    float *const la_acc = acc + (size_t)acc_row[l] * nc;
-    if (l < L - 1) {
-      LayerArgs la{(const uint8_t *)h->wpack[l], h->bias[l], h->act[cur], h->act[cur ^ 1], h->lR[l],
-                   h->lNQ[l], ncb, h->lR[l], h->n_cu, la_acc, h->widths[l + 1], nc};
-      e = launch_layer_dbg(fmt, la, s);
-    } else {
-      LastArgs ea{T, P, Y, nullptr, nullptr, nullptr, nullptr, ld, 0, nc, ncb, h->S,
-                  (const uint8_t *)h->wpack[l], h->bias[l], h->act[cur], h->lNQ[l], h->fc, h->dc,
-                  0.0, 0, 0, la_acc};
-      e = launch_last(fmt, ea, false, true, s);
-    }
-    cur ^= 1;
-  }
-  return hip_status(e);
+  return run_fused(h, a, s, &dump);
 }
 
 int32_t chem_prop_workspace_bytes(const chem_prop_desc *desc, size_t *bytes) {
@@ -1080,7 +1105,7 @@ int32_t chem_prop_eval(chem_prop *h, int64_t n, int64_t ld, const double *x, dou
     e = h->lay.pick[0] ? h->lay.pick[0](a, h->n_cu, s)
                        : h->lay.step(a, (int)(a.ntiles < h->n_cu ? a.ntiles : h->n_cu), s);
   }
-  const LayerNet net{h->prec, h->L, h->n_cu, h->lR, h->lNQ, h->wpack, h->bias, h->act};
+  const LayerNet net{h->prec, h->L, h->n_cu, h->widths, h->lR, h->lNQ, h->wpack, h->bias, h->act};
   FirstArgs fa{};
   fa.x = x;
   fa.ld = ld;

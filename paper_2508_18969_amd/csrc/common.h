@@ -223,8 +223,6 @@ struct OpF32 {
   }
   // store 4 values (already scaled) into 4 consecutive slots
   static __device__ __forceinline__ void store4(uint8_t *p, f4 v) { *(f4 *)p = v; }
-  // the operand value a stored v becomes, as FP32
-  static __device__ __forceinline__ float q(float v) { return v; }
   // one input feature: v, or fma(u, za, zc)
   static __device__ __forceinline__ float feature(double v) { return (float)v; }
   static __device__ __forceinline__ float feature(float u, float za, float zc) {
@@ -247,7 +245,6 @@ struct OpBF16 {
     o[0] = (__bf16)v[0]; o[1] = (__bf16)v[1]; o[2] = (__bf16)v[2]; o[3] = (__bf16)v[3];
     *(b4 *)p = o;
   }
-  static __device__ __forceinline__ float q(float v) { return (float)(__bf16)v; }
   // one input feature: v, or fma(u, za, zc)
   static __device__ __forceinline__ __bf16 feature(double v) { return (__bf16)to_odd(v); }
   static __device__ __forceinline__ __bf16 feature(float u, float za, float zc) {
@@ -270,7 +267,6 @@ struct OpF16 {
     o[0] = (_Float16)v[0]; o[1] = (_Float16)v[1]; o[2] = (_Float16)v[2]; o[3] = (_Float16)v[3];
     *(q4 *)p = o;
   }
-  static __device__ __forceinline__ float q(float v) { return (float)(_Float16)v; }
   // one input feature: v, or fma(u, za, zc) rounded once, to 16 bits (no FP32
   // value in between)
   static __device__ __forceinline__ _Float16 feature(double v) { return (_Float16)to_odd(v); }
@@ -313,12 +309,6 @@ struct OpF8 {
     w = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(w, __builtin_amdgcn_fmed3f(v[2], -b, b),
                                                  __builtin_amdgcn_fmed3f(v[3], -b, b), a, true);
     *(s2 *)p = w;
-  }
-  // the same clamp and conversion as pack4, decoded back to FP32
-  static __device__ __forceinline__ float q(float v) {
-    const uint32_t w = __builtin_amdgcn_cvt_pk_fp8_f32(__builtin_amdgcn_fmed3f(v, -448.0f, 448.0f),
-                                                       0.0f, 0, false);
-    return __builtin_amdgcn_cvt_f32_fp8((int)w, 0);
   }
 };
 

@@ -58,9 +58,10 @@ struct StepArgs {
   // layer dump (the kernel's debug mode): per layer l, its input operand
   // values (decoded to FP32) in rows dbg_in_row[l] .. + widths[l] of dbg_in
   // and its FP32 accumulators in rows dbg_acc_row[l] .. + widths[l+1] of
-  // dbg_acc, both [rows][n]
+  // dbg_acc, both [rows][dbg_ld]
   float *dbg_in, *dbg_acc;
   int dbg_in_row[4], dbg_acc_row[4];
+  int64_t dbg_ld;
 };
 
 // Tabulated GELU: GTAB_N intervals of width 1/GTAB_INV_H from GTAB_LO.
@@ -78,9 +79,10 @@ struct LayerArgs {
   int RO;                // row-blocks written (R up to the next layer's k-steps)
   int n_cu;              // compute units of the device
   // debug mode: FP32 accumulators of rows < dbg_rows and cells < dbg_n into
-  // dbg_acc[row * dbg_n + cell]
+  // dbg_acc[row * dbg_ld + cell]
   float *dbg_acc;
   int dbg_rows, dbg_n;
+  int64_t dbg_ld;
 };
 // First hidden layer with the input transform.
 struct FirstArgs {
@@ -96,9 +98,11 @@ struct FirstArgs {
   const double *dc;      // DConst block (property networks: PConst)
   int n_cu;              // compute units of the device
   int RPW;               // row-blocks per wave (set by the launcher)
-  // debug mode: input operand values [D][nc] and accumulators [dbg_rows][nc]
+  // debug mode: input operand values [D][dbg_ld] and accumulators
+  // [dbg_rows][dbg_ld] of cells < nc
   float *dbg_in, *dbg_acc;
   int dbg_rows;
+  int64_t dbg_ld;
 };
 // Output layer with the post-processing.
 struct LastArgs {
@@ -118,7 +122,8 @@ struct LastArgs {
   double inv_dt;
   int thermo;
   int shift;             // property networks: output k on row k + shift
-  float *dbg_acc;        // debug mode: accumulators [S][nc]
+  float *dbg_acc;        // debug mode: accumulators [S][dbg_ld] of cells < nc
+  int64_t dbg_ld;
 };
 // Property networks: FP64 constants of the input and output affine maps.
 struct PConst {
@@ -137,10 +142,10 @@ hipError_t launch_first(int fmt, const FirstArgs &a, bool prop, bool fused, bool
 hipError_t launch_layer(int fmt, const LayerArgs &a, hipStream_t s);
 hipError_t launch_last(int fmt, const LastArgs &a, bool prop, bool dbg, hipStream_t s);
 // debug: hidden layer with its accumulators dumped; the operand values of B
-// fragments X ([NQ][NCB], features < K, cells < n) decoded into out[f * n + c]
+// fragments X ([NQ][NCB], features < K, cells < n) decoded into out[f * ld + c]
 hipError_t launch_layer_dbg(int fmt, const LayerArgs &a, hipStream_t s);
 hipError_t launch_frag_decode(int fmt, const uint8_t *X, int NCB, int K, int n, float *out,
-                              hipStream_t s);
+                              int64_t ld, hipStream_t s);
 
 // Shape and layout of one compiled network configuration.
 struct NetLayout {
@@ -162,6 +167,9 @@ struct NetLayout {
   // batch's size, or null
   hipError_t (*pick[3])(const StepArgs &, int n_cu, hipStream_t);
   hipError_t (*pick_prepare[3])();
+  // its layer dump (tanh GELU): the same choice
+  hipError_t (*pick_dbg)(const StepArgs &, int n_cu, hipStream_t);
+  hipError_t (*pick_dbg_prepare)();
   int pick_species;
 };
 // The same for the kernel's property mode (hidden widths h1, h2, h3); only

@@ -308,7 +308,7 @@ __global__ __launch_bounds__(T::NT, 1) void layer_kernel(LayerArgs a) {
         for (int r = 0; r < 4; ++r) {
           const int row = 16 * (rb0 + wr * WRB + i) + 4 * g + r;
           const int cell = 16 * (cb0 + wc * WCB + j) + cl;
-          if (row < a.dbg_rows && cell < a.dbg_n) a.dbg_acc[(size_t)row * a.dbg_n + cell] = acc[i][j][r];
+          if (row < a.dbg_rows && cell < a.dbg_n) a.dbg_acc[row * a.dbg_ld + cell] = acc[i][j][r];
         }
   }
   // GELU, then the next layer's B fragments: output row 16 rb + 4 g + r is
@@ -409,7 +409,7 @@ __global__ __launch_bounds__(256) void first_kernel(FirstArgs a) {
       }
       z = used ? z : (elem_t)0.0f;
       if constexpr (DBG)
-        if (used && blockIdx.x % quads == 0) a.dbg_in[(size_t)f * a.nc + cell] = (float)z;
+        if (used && blockIdx.x % quads == 0) a.dbg_in[f * a.dbg_ld + cell] = (float)z;
       buf[j] = z;
     }
     uint8_t *const p = feat + (c * NQ + 2 * v / NE) * FB + lane * 16 + 2 * v % NE * Op::EB;
@@ -458,7 +458,7 @@ __global__ __launch_bounds__(256) void first_kernel(FirstArgs a) {
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             const int row = 16 * (rb + k) + 4 * g + r, cell = 16 * cb + cl;
-            if (row < a.dbg_rows && cell < a.nc) a.dbg_acc[(size_t)row * a.nc + cell] = acc[k][c][r];
+            if (row < a.dbg_rows && cell < a.nc) a.dbg_acc[row * a.dbg_ld + cell] = acc[k][c][r];
           }
       f4 y[RPQ];
 #pragma unroll
@@ -537,7 +537,7 @@ __global__ __launch_bounds__(256) void last_kernel(LastArgs a) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int s = 16 * h + 4 * g + r - 2;
-        if (valid && s >= 0 && s < a.S) a.dbg_acc[(size_t)s * a.nc + cell] = o[h][r];
+        if (valid && s >= 0 && s < a.S) a.dbg_acc[s * a.dbg_ld + cell] = o[h][r];
       }
   } else if constexpr (PROP) {
     if (!valid) return;
@@ -570,14 +570,14 @@ __global__ __launch_bounds__(256) void last_kernel(LastArgs a) {
 // inverse of frag_feature within a k-step, f = KS q + 16 (j / 4) + 4 g + j % 4.
 template <class Op>
 __global__ __launch_bounds__(256) void frag_decode_kernel(const uint8_t *X, int NCB, int K, int n,
-                                                          float *out) {
+                                                          float *out, int64_t ld) {
   const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (t >= (int64_t)K * n) return;
   const int f = (int)(t / n), c = (int)(t % n);
   const int q = f / Op::KS, rr = f % Op::KS;
   const int j = 4 * (rr / 16) + rr % 4, g = (rr % 16) / 4;
   const uint8_t *p = X + ((size_t)(q * NCB + c / 16) * 64 + g * 16 + c % 16) * 16 + j * Op::EB;
-  out[t] = (float)*(const decltype(Op::feature(0.0)) *)p;
+  out[f * ld + c] = (float)*(const decltype(Op::feature(0.0)) *)p;
 }
 
 // ------------------------------------------------------------------ launchers
@@ -677,14 +677,14 @@ hipError_t launch_layer_dbg(int fmt, const LayerArgs &a, hipStream_t s) {
 }
 
 hipError_t launch_frag_decode(int fmt, const uint8_t *X, int NCB, int K, int n, float *out,
-                              hipStream_t s) {
+                              int64_t ld, hipStream_t s) {
   const int64_t total = (int64_t)K * n;
   if (total <= 0) return hipSuccess;
   const dim3 grid((unsigned)((total + 255) / 256));
   switch (fmt) {
-    case 0: hipLaunchKernelGGL(frag_decode_kernel<OpF32>, grid, dim3(256), 0, s, X, NCB, K, n, out); break;
-    case 1: hipLaunchKernelGGL(frag_decode_kernel<OpBF16>, grid, dim3(256), 0, s, X, NCB, K, n, out); break;
-    case 2: hipLaunchKernelGGL(frag_decode_kernel<OpF16>, grid, dim3(256), 0, s, X, NCB, K, n, out); break;
+    case 0: hipLaunchKernelGGL(frag_decode_kernel<OpF32>, grid, dim3(256), 0, s, X, NCB, K, n, out, ld); break;
+    case 1: hipLaunchKernelGGL(frag_decode_kernel<OpBF16>, grid, dim3(256), 0, s, X, NCB, K, n, out, ld); break;
+    case 2: hipLaunchKernelGGL(frag_decode_kernel<OpF16>, grid, dim3(256), 0, s, X, NCB, K, n, out, ld); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -730,7 +730,7 @@ template <class Op> hipError_t launch_first_op(const FirstArgs &a0, bool prop, b
   const int64_t parts = (a.RO + a.RPW - 1) / a.RPW;
   const dim3 grid((unsigned)(groups * ((parts + 3) / 4)));
   auto k = prop ? first_kernel<Op, true, false>
-           : fused ? first_kernel<Op, false, true>
+           : fused ? (dbg ? first_kernel<Op, false, true, true> : first_kernel<Op, false, true>)
            : dbg ? first_kernel<Op, false, false, true> : first_kernel<Op, false, false>;
   hipLaunchKernelGGL(k, grid, dim3(256), 0, s, a);
   return hipGetLastError();

@@ -13,6 +13,7 @@ using Large29 = Cfg<OpF8, 4, 8, 1600, 800, 400>;
 using Small29 = Cfg<OpF8, 3, 8, 1600, 800, 400>;
 static_assert(Large29::R2 <= Small29::R2 && Large29::R3 <= Small29::R3 && Large29::NQ2 == Small29::NQ2 &&
               Large29::NQ3 == Small29::NQ3 && Large29::NQ4 == Small29::NQ4, "one packed layout");
+constexpr TileTime kTime29L = {16000, 39000}, kTime29S = {12000, 32000};
 
 // Compiled network shapes: the 17-species net (400, 200, 100) and the
 // 29-species net (1600, 800, 400).
@@ -24,9 +25,13 @@ bool find_layout_fp8(int h1, int h2, int h3, NetLayout *out) {
   if (h1 == 1600 && h2 == 800 && h3 == 400) {
     fill_layout<Small29, false>(out);
     out->pick[0] = [](const StepArgs &a, int n_cu, hipStream_t s) {
-      return launch_by_size<Large29, Small29, false>(a, n_cu, {16000, 39000}, {12000, 32000}, s);
+      return launch_by_size<Large29, Small29, false>(a, n_cu, kTime29L, kTime29S, s);
     };
     out->pick_prepare[0] = [] { return set_lds_limit<Large29, false, 0>(); };
+    out->pick_dbg = [](const StepArgs &a, int n_cu, hipStream_t s) {
+      return launch_by_size<Large29, Small29, false, true>(a, n_cu, kTime29L, kTime29S, s);
+    };
+    out->pick_dbg_prepare = [] { return set_lds_limit<Large29, false, 0, false, true>(); };
     out->pick_species = 30;
     return true;
   }

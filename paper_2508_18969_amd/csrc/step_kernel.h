@@ -187,6 +187,23 @@ __device__ __forceinline__ unsigned opaque_u(unsigned v) {
   asm volatile("" : "+s"(v));
   return v;
 }
+// Layer dump: value v of row `row` of a cell into buf[row * ld + cell] if ok.  A
+// store of every lane, past the resource's end (and so dropped) where it is not
+// wanted, instead of a branch: with branches amid its activations the FP8
+// kernel's debug build, which spills hundreds of registers, computed wrong
+// layer-2 activations in the lanes of a ragged last tile.
+__device__ __forceinline__ void dump_store(float *buf, int64_t ld, int row, int64_t cell, bool ok, float v) {
+  const rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(buf, (short)0, 0x7fffffff, 0x00020000);
+  const uint32_t o = ok ? ((uint32_t)row * (uint32_t)ld + (uint32_t)cell) * 4u : 0x80000000u;
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, (int)o, 0, 0);
+}
+// The value of slot r of the operands stored at p - read back, not the stored
+// value again, whose last rounding the compiler may fuse another way.
+template <class Op> __device__ __forceinline__ float stored_operand(const uint8_t *p, int r) {
+  asm volatile("" ::: "memory");
+  if constexpr (Op::EB == 1) return __builtin_amdgcn_cvt_f32_fp8((int)p[r], 0);
+  else return (float)((const decltype(Op::feature(0.0)) *)p)[r];
+}
 // PROP: property mode - the input features are the Z-scored fields x[f]
 // (f < D) and the output rows 2 .. K+1 are scaled to y[k] = o sigma_k + mu_k;
 // dc is then a PConst block.
@@ -203,7 +220,7 @@ __global__ __launch_bounds__(C::NW * 64, 1) void chem_step_kernel(StepArgs a) {
   using S3 = typename C::S3;
   constexpr int CB = C::CB, KS = C::KS, FRAG = C::FRAG, EB = C::EB, RPQ = C::RPQ;
   extern __shared__ __align__(16) uint8_t smem[];
-  constexpr bool SPLIT = C::SPLIT && GT == 0 && !CALIB && !DBG;
+  constexpr bool SPLIT = C::SPLIT && GT == 0 && !CALIB;
   uint8_t *const A0 = smem + (SPLIT ? C::LDS_BYTES : C::LDS_A0);
   uint8_t *const A1 = smem + C::LDS_A1;
   uint8_t *const A2 = smem + C::LDS_A2;
@@ -257,9 +274,9 @@ __global__ __launch_bounds__(C::NW * 64, 1) void chem_step_kernel(StepArgs a) {
     else return gelu(x);
   };
   // debug mode: value v of output row `row` (< rows) of a cell into
-  // buf[(row0 + row) * n + cell]
+  // buf[(row0 + row) * dbg_ld + cell]
   auto dbg_put = [&](float *buf, int row0, int row, int rows, int64_t cell, float v) {
-    if (row < rows && cell < a.n) buf[(int64_t)(row0 + row) * a.n + cell] = v;
+    dump_store(buf, a.dbg_ld, row0 + row, cell, row < rows && cell < a.n, v);
   };
   __syncthreads();
 
@@ -332,8 +349,6 @@ __global__ __launch_bounds__(C::NW * 64, 1) void chem_step_kernel(StepArgs a) {
         z = valid ? z : 0.0f;
         if (CALIB) amx[0] = umaxf(amx[0], __builtin_fabsf(z));
         v[h][r] = z * inv_sa[0];
-        if constexpr (DBG)
-          if (valid && f < a.S + 2) a.dbg_in[(int64_t)(a.dbg_in_row[0] + f) * a.n + i] = Op::q(v[h][r]);
       }
     if constexpr (KS == 16) {
       // two k-steps of 16: feature 16h + 4g + r sits in k-step h, slot r
@@ -347,6 +362,13 @@ __global__ __launch_bounds__(C::NW * 64, 1) void chem_step_kernel(StepArgs a) {
 #pragma unroll
       for (int o = 8 * EB; o < FRAG; o += 4) *(uint32_t *)(p + o) = 0u;
     }
+    if constexpr (DBG)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const uint8_t *p = A0 + ((KS == 16 ? j / 4 * CB : 0) + wp) * 64 * FRAG + lane * FRAG;
+        dbg_put(a.dbg_in, a.dbg_in_row[0], 16 * (j / 4) + 4 * g + j % 4, a.S + 2, i,
+                stored_operand<Op>(p, KS == 16 ? j % 4 : j));
+      }
   };
   if (SPLIT && prew) put_features(blockIdx.x);
 
@@ -432,11 +454,13 @@ __global__ __launch_bounds__(C::NW * 64, 1) void chem_step_kernel(StepArgs a) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) amx[1] = umaxf(amx[1], __builtin_fabsf(y[k]));
           // (scaled formats: y / a_1 is quantised by the store)
+          const int q2l = rbl / RPQ, j0 = 4 * (rbl % RPQ);
+          uint8_t *const p = (A1 + cb * 64 * FRAG) + (dv + (q2l * CB * 64 * FRAG + j0 * EB));
+          Op::store4s(p, y, sa[1]);
           if constexpr (DBG)
 #pragma unroll
-            for (int k = 0; k < 4; ++k) dbg_put(a.dbg_in, a.dbg_in_row[1], 16 * rb + 4 * g + k, C::H1, cell0 + 16 * cb + cl, Op::q(y[k] * inv_sa[1]));
-          const int q2l = rbl / RPQ, j0 = 4 * (rbl % RPQ);
-          Op::store4s((A1 + cb * 64 * FRAG) + (dv + (q2l * CB * 64 * FRAG + j0 * EB)), y, sa[1]);
+            for (int k = 0; k < 4; ++k)
+              dbg_put(a.dbg_in, a.dbg_in_row[1], 16 * rb + 4 * g + k, C::H1, cell0 + 16 * cb + cl, stored_operand<Op>(p, k));
         }
       }
     };
@@ -489,16 +513,18 @@ __global__ __launch_bounds__(C::NW * 64, 1) void chem_step_kernel(StepArgs a) {
           if (CALIB && cell0 + 16 * cb + cl < a.n)
 #pragma unroll
             for (int j = 0; j < 4; ++j) amx[1] = umaxf(amx[1], __builtin_fabsf(y[j]));
-          if constexpr (DBG)
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-              dbg_put(a.dbg_in, a.dbg_in_row[1], 16 * (sc * (C::SC / 16) + rbl) + 4 * g + k, C::H1, cell0 + 16 * cb + cl, Op::q(y[k] * inv_sa[1]));
           const int q2l = rbl / RPQ, j0 = 4 * (rbl % RPQ);
           // (the store's lane offset is taken here, where it is used: an
           // opaque copy per call of this function costs a move per group;
           // scaled formats: y / a_1 is quantised by the store)
           const int dv = opaque_v(buf * C::QSC * C::QBYTES + lane * FRAG);
-          Op::store4s((A1 + cb * 64 * FRAG) + (dv + (q2l * CB * 64 * FRAG + j0 * EB)), y, sa[1]);
+          uint8_t *const p = (A1 + cb * 64 * FRAG) + (dv + (q2l * CB * 64 * FRAG + j0 * EB));
+          Op::store4s(p, y, sa[1]);
+          if constexpr (DBG)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              dbg_put(a.dbg_in, a.dbg_in_row[1], 16 * (sc * (C::SC / 16) + rbl) + 4 * g + j, C::H1,
+                      cell0 + 16 * cb + cl, stored_operand<Op>(p, j));
         }
         // keeps the operation in its group
         asm volatile("" : "+v"(ts[v]));
@@ -680,7 +706,9 @@ __global__ __launch_bounds__(C::NW * 64, 1) void chem_step_kernel(StepArgs a) {
     auto lane_a = [&]() { return FRAG == 32 ? opaque_v(lane) : lane; };
     // (scaled formats: y / as is quantised by the store)
     auto put = [&](uint8_t *base, int rb, int cb, f4 y, float as) {
-      Op::store4s(base + (((rb / RPQ) * CB + cb) * 64 + lane_a()) * FRAG + 4 * (rb % RPQ) * EB, y, as);
+      uint8_t *const p = base + (((rb / RPQ) * CB + cb) * 64 + lane_a()) * FRAG + 4 * (rb % RPQ) * EB;
+      Op::store4s(p, y, as);
+      return p;
     };
     // rows past the computed ones, up to the next k-step boundary, are zero
     auto zero_pad = [&](int r0, int r1) {
@@ -726,11 +754,13 @@ __global__ __launch_bounds__(C::NW * 64, 1) void chem_step_kernel(StepArgs a) {
             for (int r = 0; r < 4; ++r) amx[2] = umaxf(amx[2], __builtin_fabsf(y[r]));
           if constexpr (DBG)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
+            for (int r = 0; r < 4; ++r)
               dbg_put(a.dbg_acc, a.dbg_acc_row[1], 16 * rb + 4 * g + r, C::H2, cell0 + 16 * cb + cl, acc2[t][r]);
-              dbg_put(a.dbg_in, a.dbg_in_row[2], 16 * rb + 4 * g + r, C::H2, cell0 + 16 * cb + cl, Op::q(y[r] * inv_sa[2]));
-            }
-          put(A2, rb, cb, y, sa[2]);
+          const uint8_t *const p = put(A2, rb, cb, y, sa[2]);
+          if constexpr (DBG)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              dbg_put(a.dbg_in, a.dbg_in_row[2], 16 * rb + 4 * g + r, C::H2, cell0 + 16 * cb + cl, stored_operand<Op>(p, r));
         }
         // FP8: two tiles at a time, which keeps the accumulators where they
         // are instead of letting the scheduler copy them all out of the
@@ -854,11 +884,13 @@ __global__ __launch_bounds__(C::NW * 64, 1) void chem_step_kernel(StepArgs a) {
             for (int r = 0; r < 4; ++r) amx[3] = umaxf(amx[3], __builtin_fabsf(y[r]));
           if constexpr (DBG)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
+            for (int r = 0; r < 4; ++r)
               dbg_put(a.dbg_acc, a.dbg_acc_row[2], 16 * rb + 4 * g + r, C::H3, cell0 + 16 * cb + cl, acc3[t][r]);
-              dbg_put(a.dbg_in, a.dbg_in_row[3], 16 * rb + 4 * g + r, C::H3, cell0 + 16 * cb + cl, Op::q(y[r] * inv_sa[3]));
-            }
-          put(A2, rb, cb, y, sa[3]);
+          const uint8_t *const p = put(A2, rb, cb, y, sa[3]);
+          if constexpr (DBG)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              dbg_put(a.dbg_in, a.dbg_in_row[3], 16 * rb + 4 * g + r, C::H3, cell0 + 16 * cb + cl, stored_operand<Op>(p, r));
         }
         if (FRAG == 32 && (t0 & 1)) __builtin_amdgcn_sched_barrier(0);
       }
@@ -904,7 +936,7 @@ __global__ __launch_bounds__(C::NW * 64, 1) void chem_step_kernel(StepArgs a) {
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             const int s = 16 * h + 4 * g + r - 2;
-            if (vpost && s >= 0 && s < a.S) a.dbg_acc[(int64_t)(a.dbg_acc_row[3] + s) * a.n + ipost] = o[h][r];
+            dump_store(a.dbg_acc, a.dbg_ld, a.dbg_acc_row[3] + s, ipost, vpost && s >= 0 && s < a.S, o[h][r]);
           }
         continue;
       }
@@ -981,7 +1013,7 @@ static hipError_t launch_calib(const StepArgs &a, int grid, hipStream_t s) {
 template <class C>
 static hipError_t launch_dbg(const StepArgs &a, int grid, hipStream_t s) {
   hipLaunchKernelGGL((chem_step_kernel<C, false, 0, false, true>), dim3(grid), dim3(C::NW * 64),
-                     C::lds_bytes(0), s, a);
+                     C::lds_split(), s, a);
   return hipGetLastError();
 }
 template <class C, bool CALIB, int GT, bool PROP = false, bool DBG = false>
@@ -1048,13 +1080,14 @@ static void fill_prop_layout(NetLayout *L) {
 // Tiles of 64 (CL) or 48 cells (CS) by the batch's size: the fewer nanoseconds
 // of first + rounds * per.
 struct TileTime { int first, per; };
-template <class CL, class CS, bool PROP>
+template <class CL, class CS, bool PROP, bool DBG = false>
 static hipError_t launch_by_size(const StepArgs &a0, int n_cu, TileTime l, TileTime s, hipStream_t st) {
   auto rounds = [&](int mc) { return ((a0.n + mc - 1) / mc + n_cu - 1) / n_cu; };
   const bool small = s.first + rounds(CS::MC) * s.per < l.first + rounds(CL::MC) * l.per;
   StepArgs a = a0;
   a.ntiles = (a.n + (small ? CS::MC : CL::MC) - 1) / (small ? CS::MC : CL::MC);
   const int grid = (int)(a.ntiles < n_cu ? a.ntiles : n_cu);
+  if constexpr (DBG) return small ? launch_dbg<CS>(a, grid, st) : launch_dbg<CL>(a, grid, st);
   return small ? launch_step<CS, 0, PROP>(a, grid, st) : launch_step<CL, 0, PROP>(a, grid, st);
 }
 

@@ -76,7 +76,9 @@ template <class C_, int CB_, int GT_> struct Small {
   static constexpr int PF = CB == 1 ? 8 : 6;
 };
 
-template <class S>
+// DBG: layer dump, as in the fused kernel - input operand values as they were
+// stored (decoded to FP32) and accumulators of every layer; no post-processing.
+template <class S, bool DBG = false>
 __global__ __launch_bounds__(S::NW * 64, 2) void small_step_kernel(StepArgs a) {
   using C = typename S::C;
   using Op = typename C::Op;
@@ -197,6 +199,13 @@ __global__ __launch_bounds__(S::NW * 64, 2) void small_step_kernel(StepArgs a) {
   }
   __syncthreads();
 
+  // debug mode: value v of row `row` (0 .. rows - 1) of a cell into
+  // buf[(row0 + row) * dbg_ld + cell]
+  auto dbg_put = [&](float *buf, int row0, int row, int rows, int64_t cell, float v) {
+    dump_store(buf, a.dbg_ld, row0 + row, cell, row >= 0 && row < rows && cell < a.n, v);
+  };
+  int64_t cell0 = 0;                                   // first cell of the tile
+
   // input transform of the tile whose fields are in xin: state to LDS for the
   // post-processing, features to A0 (rounded as in the fused kernel), where
   // fields 16 .. 19 are slots 4 .. 7 (FP32: slots of the second k-step) of
@@ -249,6 +258,11 @@ __global__ __launch_bounds__(S::NW * 64, 2) void small_step_kernel(StepArgs a) {
     }
     if constexpr (EB == 2) *(uint64_t *)own = *(const uint64_t *)own4;
     else Op::store4(own, v);
+    if constexpr (DBG)
+#pragma unroll
+      for (int j = 0; j < SLOTS; ++j)
+        dbg_put(a.dbg_in, a.dbg_in_row[0], row_of(j >> 2, j & 3, g), a.S + 2, t * S::MC + 16 * uc + cl,
+                j < 4 ? stored_operand<Op>(own, j) : stored_operand<Op>(tail, 0));
   };
 
   using std::integral_constant;
@@ -290,7 +304,24 @@ __global__ __launch_bounds__(S::NW * 64, 2) void small_step_kernel(StepArgs a) {
     if constexpr (!Op::SCALED)
 #pragma unroll
       for (int r = 0; r < 4; ++r) asm("" : "+v"(y[r]));
-    Op::store4s(A + ((unsigned)rb / RPQ * CB + cb) * FB + voff + 4 * ((unsigned)rb % RPQ) * EB, y, sa[l + 1]);
+    uint8_t *const p = A + ((unsigned)rb / RPQ * CB + cb) * FB + voff + 4 * ((unsigned)rb % RPQ) * EB;
+    Op::store4s(p, y, sa[l + 1]);
+    if constexpr (DBG)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        dbg_put(a.dbg_in, a.dbg_in_row[l + 1], 16 * rb + 4 * g + r, l == 0 ? C::H1 : l == 1 ? C::H2 : C::H3,
+                cell0 + 16 * cb + cl, stored_operand<Op>(p, r));
+  };
+  // debug mode: layer l's accumulators z
+  auto dump_acc = [&](f4 z, int l, int rb, int cb) {
+    if constexpr (DBG)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        // (the output layer's second row-block: row 16 + g in slot 0)
+        const int row = l < 3 ? 16 * rb + 4 * g + r : rb == 0 || r == 0 ? row_of(rb, r, g) - 2 : -1;
+        const int H = l == 0 ? C::H1 : l == 1 ? C::H2 : l == 2 ? C::H3 : a.S;
+        dbg_put(a.dbg_acc, a.dbg_acc_row[l], row, H, cell0 + 16 * cb + cl, z[r]);
+      }
   };
   auto scale = [&](f4 &y, int l, const float *B, int rb) {
     if constexpr (Op::SCALED) {
@@ -309,6 +340,7 @@ __global__ __launch_bounds__(S::NW * 64, 2) void small_step_kernel(StepArgs a) {
 
   for (int64_t tile = blockIdx.x; tile < a.ntiles; tile += gridDim.x, buf ^= 1) {
     renew();
+    if constexpr (DBG) cell0 = tile * S::MC;
     // ------------------------------------------------------------ layer 1
     if constexpr (S::STREAM) {
       if (low || pre) {
@@ -347,7 +379,11 @@ __global__ __launch_bounds__(S::NW * 64, 2) void small_step_kernel(StepArgs a) {
               [&](int u) { return u < G * CB ? xq[q][u % CB] : xe; }, [&](int u) -> f4 & { return z[u]; });
         }
 #pragma unroll
-        for (int u = 0; u < N; ++u) scale(z[u], 0, B1, u < G * CB ? 3 * w + k0 + u / CB : 24);
+        for (int u = 0; u < N; ++u) {
+          const int rb = u < G * CB ? 3 * w + k0 + u / CB : 24;
+          dump_acc(z[u], 0, rb, u < G * CB ? u % CB : uc);
+          scale(z[u], 0, B1, rb);
+        }
         act(z, N);
 #pragma unroll
         for (int u = 0; u < N; ++u)
@@ -403,7 +439,12 @@ __global__ __launch_bounds__(S::NW * 64, 2) void small_step_kernel(StepArgs a) {
       else if (pre) run(integral_constant<int, 1>{});
       else run(integral_constant<int, 0>{});
 #pragma unroll
-      for (int c = 0; c < CB; ++c) scale(z0[c], 1, B2, w), scale(z1[c], 1, B2, rb2b);
+      for (int c = 0; c < CB; ++c) {
+        dump_acc(z0[c], 1, w, c);
+        if (low) dump_acc(z1[c], 1, rb2b, c);
+        else if (pre && c == 0) dump_acc(z1[0], 1, rb2b, uc);
+        scale(z0[c], 1, B2, w), scale(z1[c], 1, B2, rb2b);
+      }
       act(z0, CB);
 #pragma unroll
       for (int c = 0; c < CB; ++c) put(z0[c], 1, w, c, A2);
@@ -432,7 +473,7 @@ __global__ __launch_bounds__(S::NW * 64, 2) void small_step_kernel(StepArgs a) {
               [&](int c) -> f4 & { return z[c]; });
         }
 #pragma unroll
-        for (int c = 0; c < CB; ++c) scale(z[c], 2, B3, w);
+        for (int c = 0; c < CB; ++c) dump_acc(z[c], 2, w, c), scale(z[c], 2, B3, w);
         act(z, CB);
 #pragma unroll
         for (int c = 0; c < CB; ++c) put(z[c], 2, w, c, A3);
@@ -458,9 +499,10 @@ __global__ __launch_bounds__(S::NW * 64, 2) void small_step_kernel(StepArgs a) {
             [&](int h) -> f4 & { return o[h]; });
       }
 #pragma unroll
-      for (int h = 0; h < 2; ++h) scale(o[h], 3, B4, h);
+      for (int h = 0; h < 2; ++h) dump_acc(o[h], 3, h, w), scale(o[h], 3, B4, h);
       const int64_t i = tile * S::MC + 16 * w + cl;
       const bool valid = i < a.n;
+      if constexpr (!DBG) {
       const double *st = (const double *)(smem + S::LDS_ST + buf * S::ST_BYTES) + w * 64 * S::STL;
       const double T = st[cl * S::STL], P = st[cl * S::STL + 1];
       double Yc[SLOTS];
@@ -471,6 +513,7 @@ __global__ __launch_bounds__(S::NW * 64, 2) void small_step_kernel(StepArgs a) {
 #define POST_ROW(h, r, g) row_of(h, r, g)
 #define POST_AT(h, r, g, s) row_at(h, r, g, i)
 #include "post.inc"
+      }
     } else if (pre && tile + gridDim.x < a.ntiles) {
       preprocess(tile + gridDim.x, buf ^ 1);
       load_xin(tile + 2 * (int64_t)gridDim.x);
@@ -479,11 +522,11 @@ __global__ __launch_bounds__(S::NW * 64, 2) void small_step_kernel(StepArgs a) {
   }
 }
 
-template <class S> static hipError_t launch_small(const StepArgs &a0, int n_cu, hipStream_t s) {
+template <class S, bool DBG> static hipError_t launch_small(const StepArgs &a0, int n_cu, hipStream_t s) {
   StepArgs a = a0;
   a.ntiles = (a.n + S::MC - 1) / S::MC;
   const int grid = (int)(a.ntiles < n_cu ? a.ntiles : n_cu);
-  hipLaunchKernelGGL((small_step_kernel<S>), dim3(grid), dim3(S::NW * 64), S::LDS_BYTES, s, a);
+  hipLaunchKernelGGL((small_step_kernel<S, DBG>), dim3(grid), dim3(S::NW * 64), S::LDS_BYTES, s, a);
   return hipGetLastError();
 }
 
@@ -491,21 +534,22 @@ template <class S> static hipError_t launch_small(const StepArgs &a0, int n_cu, 
 // MAXCB (four; two in FP32, whose four blocks do not fit the LDS).  A tile of one
 // / two / four blocks takes 4.0 / 5.8 / 8.9 us in BF16, 4.1 / 5.3 / 8.5 in FP8,
 // 13.8 / 20.8 in FP32, so the fewest rounds are the fastest.
-template <class C, int MAXCB, int GT> static hipError_t small_step(const StepArgs &a, int n_cu, hipStream_t s) {
+template <class C, int MAXCB, int GT, bool DBG = false>
+static hipError_t small_step(const StepArgs &a, int n_cu, hipStream_t s) {
   const int64_t blocks = (a.n + 15) / 16;
-  if (blocks <= n_cu) return launch_small<Small<C, 1, GT>>(a, n_cu, s);
-  if (MAXCB == 2 || blocks <= 2 * n_cu) return launch_small<Small<C, 2, GT>>(a, n_cu, s);
-  return launch_small<Small<C, MAXCB, GT>>(a, n_cu, s);
+  if (blocks <= n_cu) return launch_small<Small<C, 1, GT>, DBG>(a, n_cu, s);
+  if (MAXCB == 2 || blocks <= 2 * n_cu) return launch_small<Small<C, 2, GT>, DBG>(a, n_cu, s);
+  return launch_small<Small<C, MAXCB, GT>, DBG>(a, n_cu, s);
 }
 
-template <class S> static hipError_t small_lds() {
-  return hipFuncSetAttribute((const void *)small_step_kernel<S>, hipFuncAttributeMaxDynamicSharedMemorySize,
+template <class S, bool DBG> static hipError_t small_lds() {
+  return hipFuncSetAttribute((const void *)small_step_kernel<S, DBG>, hipFuncAttributeMaxDynamicSharedMemorySize,
                              S::LDS_BYTES);
 }
-template <class C, int MAXCB, int GT> static hipError_t small_prepare() {
-  hipError_t e = small_lds<Small<C, 1, GT>>();
-  if (e == hipSuccess) e = small_lds<Small<C, 2, GT>>();
-  if (e == hipSuccess && MAXCB > 2) e = small_lds<Small<C, MAXCB, GT>>();
+template <class C, int MAXCB, int GT, bool DBG = false> static hipError_t small_prepare() {
+  hipError_t e = small_lds<Small<C, 1, GT>, DBG>();
+  if (e == hipSuccess) e = small_lds<Small<C, 2, GT>, DBG>();
+  if (e == hipSuccess && MAXCB > 2) e = small_lds<Small<C, MAXCB, GT>, DBG>();
   return e;
 }
 template <class C, bool WITH_CALIB, int MAXCB> static void fill_small_layout(NetLayout *L) {
@@ -516,6 +560,8 @@ template <class C, bool WITH_CALIB, int MAXCB> static void fill_small_layout(Net
   L->pick_prepare[0] = small_prepare<C, MAXCB, 0>;
   L->pick_prepare[1] = small_prepare<C, MAXCB, 1>;
   L->pick_prepare[2] = small_prepare<C, MAXCB, 2>;
+  L->pick_dbg = small_step<C, MAXCB, 0, true>;
+  L->pick_dbg_prepare = small_prepare<C, MAXCB, 0, true>;
   L->pick_species = 18;                              // its slots
 }
 
