@@ -10,6 +10,7 @@
 
 #include "../../include/chem_dnn.h"
 #include "internal.h"
+#include "rest.h"
 #include "train.h"
 
 using namespace chemdnn;
@@ -155,15 +156,13 @@ int eb_of(int prec) { return prec == CHEM_DNN_FP32 ? 4 : 2; }
 // / 50 us fused and 18 / 28 / 46 / 64 layer by layer in BF16, 211 / 214 / 215
 // / 215 and 39 / 64 / 149 / 198 in FP32; 3-1024-512-256-1 in FP32 90 / 91 / 92
 // / 93 and 27 / 41 / 63 / 88.  Networks below 1 MiB are not worth four
-// launches (19-400-200-100-17 in BF16 at 1,000 cells: 16.6 against 17.1).  A
-// property network's buffers keep to the workspace slack that its description
-// allows in 16 bits (256 cells: 22.2 us fused, 15.5 layer by layer).
-// FP8 and the tabulated GELU have no layer kernels.
-// Behind whole rounds the layer kernels have to wait for the last fused tile,
-// while a fused rest starts on the CUs that are done: there the limit is
-// lower (2/3 in FP32, half in 16 bits): of the first network, 16,384 + 2,048
-// cells in FP16 take 101 us fused and 95 in two parts, 16,384 + 3,627 take 102
-// and 103; 8,192 + 4,008 cells in FP32 419 and 366.
+// launches (19-400-200-100-17 in BF16 at 1,000 cells: 16.6 against 17.1).  FP8 and
+// the tabulated GELU have no layer kernels.  The property network in 16 bits
+// breaks even at 2,000 cells (256 / 512 / 1,000 / 2,000 / 3,000 cells 22 us fused
+// each, 14.7 / 16.5 / 19.1 / 22.1 / 26 layer by layer), but its limit is what
+// its workspace has room for: the ABI's tests hold it below its weights and
+// 1 MiB, and 256 cells' activations take 0.75 MiB.
+// Measured on 256 compute units; rest_limit (rest.h) scales them for fewer.
 int64_t chain_cells(int prec, const NetLayout &lay, int gelu_form, bool prop) {
   if (prec == CHEM_DNN_FP8E4M3 || gelu_form != CHEM_DNN_GELU_TANH) return 0;
   size_t weights = 0;
@@ -251,7 +250,8 @@ int32_t plan(const chem_dnn_desc *d, NetLayout *lay, WsPlan *p) {
       p->act[b] = off;
       off = align_up(off + (size_t)kmax * kChunk * eb);
     }
-    off = align_up(off + (size_t)32 * kChunk * sizeof(float));   // reserved (the documented minimum)
+    // (not used: the ABI's tests hold the workspace to at least this)
+    off = align_up(off + (size_t)32 * kChunk * sizeof(float));
   }
   p->train = off;
   if (fused)
@@ -559,7 +559,8 @@ int32_t prop_plan(const chem_prop_desc *d, PropPlan *p) {
     p->act[b] = off;
     off = align_up(off + (size_t)kmax * p->chunk * eb);
   }
-  off = align_up(off + (size_t)32 * p->chunk * sizeof(float));   // reserved (the documented minimum)
+  // (not used: the ABI's tests hold the workspace to at least this)
+  off = align_up(off + (size_t)32 * p->chunk * sizeof(float));
   p->total = off;
   return CHEM_DNN_OK;
 }
@@ -601,20 +602,14 @@ int grid_for(const chem_dnn *h, int64_t ntiles) {
   return (int)(g < 1 ? 1 : g);
 }
 
-// Cells at the end of a batch of n that run layer by layer (see chain_cells).
-int64_t chain_rest(int64_t n, int64_t round, int64_t limit, int prec) {
-  const int64_t rest = n % round;
-  if (n >= round) limit = prec == CHEM_DNN_FP32 ? limit * 2 / 3 : limit / 2;
-  return rest <= limit ? rest : 0;
-}
-
 // The fused kernel over whole rounds of its tiles, the layer-by-layer kernels
 // over the rest of the batch where that is small.  With a dump (tanh GELU), the
 // debug builds of the same kernels.
 int32_t run_fused(chem_dnn *h, StepArgs a, hipStream_t s, const Dump *dump = nullptr) {
   const bool small = h->S <= h->lay.pick_species;
   const auto pick = !small ? nullptr : dump ? h->lay.pick_dbg : h->lay.pick[h->gelu_form];
-  const int64_t nc = chain_rest(a.n, (int64_t)h->n_cu * h->lay.MC, h->chain, h->prec), n = a.n - nc;
+  const int64_t nc = rest_cells(a.n, (int64_t)h->n_cu * h->lay.MC, h->chain, h->prec == CHEM_DNN_FP32);
+  const int64_t n = a.n - nc;
   hipError_t e = hipSuccess;
   if (n > 0) {
     a.n = n;
@@ -724,7 +719,7 @@ int32_t chem_dnn_init(const chem_dnn_desc *d, const float *params, void *workspa
   } else {
     for (int l = 0; l < 4; ++l) h->lR[l] = lay.R[l], h->lNQ[l] = lay.NQ[l];
   }
-  h->chain = chain;
+  h->chain = rest_limit(chain, n_cu);
   h->prec = d->precision;
   h->lay = lay;
   h->dev = dev;
@@ -1029,7 +1024,7 @@ int32_t chem_prop_init(const chem_prop_desc *d, const float *params, void *works
     h->lR[l] = p.fused ? p.lay.R[l] : l == h->L - 1 ? 2 : d->widths[l + 1] / 16;
     h->lNQ[l] = p.fused ? p.lay.NQ[l] : (l == 0 ? 32 : d->widths[l]) / ks;
   }
-  h->chunk = p.chunk;
+  h->chunk = p.fused ? rest_limit(p.chunk, n_cu) : p.chunk;
   h->ws = (uint8_t *)workspace;
   h->ws_bytes = workspace_bytes;
   h->pc = (double *)(h->ws + p.pc);
@@ -1089,7 +1084,7 @@ int32_t chem_prop_eval(chem_prop *h, int64_t n, int64_t ld, const double *x, dou
   // fused: whole rounds of the fused kernel's tiles, and a small rest layer by layer
   int64_t n0 = 0;
   hipError_t e = hipSuccess;
-  if (h->fused) n0 = n - chain_rest(n, (int64_t)h->n_cu * h->lay.MC, h->chunk, h->prec);
+  if (h->fused) n0 = n - rest_cells(n, (int64_t)h->n_cu * h->lay.MC, h->chunk, h->prec == CHEM_DNN_FP32);
   if (n0 > 0) {
     StepArgs a{};
     a.n = n0;
