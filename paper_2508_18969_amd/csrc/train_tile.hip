@@ -15,7 +15,10 @@
 // 2.7e-6 off at 40,000 samples, against 2.1e-7).  Against 64 bits the results
 // are closer than with FP32 products: output 1.5e-7 of its norm against
 // 3.8e-7, gradients 1.5e-7 to 2.6e-7 against 2.7e-7 to 3.7e-7 (batches of 300
-// to 65,536).  An infinite operand gives NaN.
+// to 65,536).  The range ends sooner than FP32's: operands that round to BF16
+// infinity (above 3.39e38, and infinities) give NaN, and below 1e-33 the low
+// parts become subnormal and lose bits (first layer's sums of operands of 1e-30
+// / 1e-33 / 1e-36 / 1e-39: 3.3e-8 / 3.9e-8 / 2.7e-5 / 2.6e-2 of their norm off).
 //
 // Kernels of one training step on a batch (or chunk):
 //   split_pack_kernel  weights and transposed weights -> fragments (once)
@@ -82,19 +85,6 @@ __device__ __forceinline__ f4 mma(i4 a, i4 b, f4 c) {
 // LDS traffic only (global loads stay in flight).
 __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
-// Workgroup ids are dealt round-robin to the 8 XCDs: tile (x, y) of id such
-// that the ny tiles of a column x run back to back on one XCD.
-__device__ __forceinline__ void xcd_tile(int id, int nx, int ny, int &x, int &y) {
-  if (nx % 8 == 0) {
-    const int xcd = id & 7, j = id >> 3;
-    y = j % ny;
-    x = (j / ny) * 8 + xcd;
-  } else {
-    x = id % nx;
-    y = id / nx;
-  }
 }
 
 // The scratch between the tiles and the weight gradients: per 32-sample tile a
@@ -255,8 +245,9 @@ template <int NI, int Q> struct WStream {
 // products are a chain of barriers in which all waves multiply at the same
 // time and then all evaluate: of its 60k cycles, 23k are products, 16k the
 // GELUs, splits and stores, the rest waits and the uneven share of the last
-// row-block (65,536 samples: 250 us, 112 TFLOP/s of FP32 products; the
-// layer-by-layer FP32 kernels took 570 us for the same part of the step).
+// row-block (65,536 samples: 248 us in a trace of single steps, 113 TFLOP/s of
+// FP32 products, 285 under a continuous load's lower clock; the layer-by-layer
+// FP32 kernels took 570 us for the same part of the step).
 //   LDS: A  a_1; then dO, dZ_3 (and dZ_1 for the input gradient)
 //        B  a_2; then dZ_2
 //        C  a_3
@@ -693,8 +684,10 @@ constexpr int DF = 24;                // most operand fragments of a workgroup t
 // two LDS buffers while the other's products run; each operand is loaded and
 // split once per workgroup.  (Four waves that load and split their own
 // operands read 1.1 GB for 65,536 samples and spend as long on the splits as
-// on the products: 177 us against 145 for 65,536 samples.)  db_l: the row sums of the dZ_l fragments, by the
-// waves that load them, in the tiles of the first column.
+// on the products: 177 us for 65,536 samples, against 155 in a trace of single
+// steps now, 181 under a continuous load's lower clock.)  db_l: the row sums of
+// the dZ_l fragments, by the waves that load them, in the tiles of the first
+// column.
 //
 // NI x NJ: the most blocks of a wave (the last waves' missing ones are computed
 // on other rows and not written).
