@@ -32,7 +32,11 @@
  *     the caller owns every buffer, including the workspace.
  *   - Field layout is structure-of-arrays: array[j * ld + i] holds feature or
  *     species j of cell i, ld >= n.
- *   - One handle may be used from one stream at a time.
+ *   - One handle may be used from one stream at a time: calls on a handle share
+ *     its workspace, which holds the activations between the kernels of small
+ *     batches and of networks that run layer by layer, and the packed weights
+ *     and scratch of the training path.  Calls that overlap (two streams, a
+ *     graph replayed beside another call) need a handle each.
  */
 #ifndef CHEM_DNN_H
 #define CHEM_DNN_H
@@ -173,7 +177,8 @@ int32_t chem_dnn_get_scales(chem_dnn *h, float *act_scale, float *w_scale, void 
  * entry points below are this library's own differentiable path for
  * training or fine-tuning the chemistry network on labels from a stiff
  * integrator: an FP32 forward (of the 17-species shape as products of
- * three-part BF16 splits, 24 bits, summed in FP32) that saves (or recomputes)
+ * three-part BF16 splits, 24 bits, summed in FP32; operands above 3.39e38 give
+ * NaN there and below 1e-33 have fewer bits) that saves (or recomputes)
  * the hidden pre-activations, an MSE loss on the normalised Box-Cox increment, a
  * hand-written backward of the tanh-form GELU network and Adam (Kingma & Ba,
  * Algorithm 1).  Fused network shapes only.

@@ -233,7 +233,9 @@ class ChemDNN:
     """A chemistry-update handle on the current device.
 
     params: CUDA float32 tensor, flat [W1 (out x in), b1, ..., W4, b4].
-    The workspace is a torch uint8 tensor owned by this object.
+    The workspace is a torch uint8 tensor owned by this object; calls share it, so
+    calls that overlap (on two streams, or beside a replayed graph) need an
+    object each.
     """
 
     def __init__(self, widths, precision, params, in_mean, in_std, out_mean=None, out_std=None,

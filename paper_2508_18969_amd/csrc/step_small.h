@@ -15,9 +15,10 @@
 // so every SIMD (waves w and w + 4) has as many products and GELUs as the
 // others in layers 1 and 2, and the FP64 work of both ends runs side by side.
 // The layer-2 and layer-3 weights of a wave stay in its registers (16-bit and
-// FP8 operands: 132 / 80 of the 256), those of layers 1 and 4 in LDS.  FP32
-// weights are too large for that: they come from L2 for each tile, loaded a
-// phase (layers 1, 3) or PF k-steps (layer 2) ahead.
+// FP8 operands: 132 / 80 of the 256; layer 3's are reloaded from L2 a phase
+// ahead), those of layers 1 and 4 in LDS.  FP32 weights are too large for that:
+// layers 1 and 3 stay in registers, layer 2 comes from L2 for each tile, PF
+// k-steps ahead, layer 4 lies in LDS.
 //
 // The fused kernel (step_kernel.h) has these weights stream through four waves
 // in chunks of layer 1, one barrier per chunk, and a tile of it takes the same
